@@ -450,7 +450,7 @@ typedef struct {
  * logit matrices plus the TopK bitsets.  Host only. */
 int smallkv_match_workspace_size(const smallkv_match_t *match, size_t *bytes);
 
-/* Enqueues the matching on `stream` (four kernel launches). */
+/* Enqueues the matching on `stream` (two or three kernel launches). */
 int smallkv_match(const smallkv_match_t *match, void *ws, size_t ws_bytes, void *stream);
 
 /* A static string for a status code. */

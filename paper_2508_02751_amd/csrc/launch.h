@@ -115,14 +115,11 @@ hipError_t launch_group_partition(const smallkv_batch_t &b, int group_rows, cons
 size_t store_workspace(const smallkv_store_t &s);
 hipError_t launch_store_update(const smallkv_store_t &s, void *ws, hipStream_t st);
 
-// Workspace of the prefill matching: the logit matrix S of every head
-// ([B][H][w_cap][ld] fp32, ld = w_cap rounded up to 4), the row maxima per
-// 64-token tile column ([B][H][w_cap][nt] fp32), each row's (max, sum)
-// ([B][H][w_cap] float2), then the TopK bitsets ([B][H][nw] words of 64
-// tokens).
+// Workspace of the prefill matching: the TopK bitsets ([B][H][nw] words of 64
+// tokens); total is the size the header states.
 struct MatchLayout {
-  int nw, nt, ld;
-  size_t pmax_offset, mz_offset, bits_offset, total;
+  int nw;
+  size_t total;
 };
 MatchLayout match_layout(const smallkv_match_t &m);
 hipError_t launch_match(const smallkv_match_t &m, void *ws, hipStream_t st);

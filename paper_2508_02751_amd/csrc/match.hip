@@ -11,21 +11,24 @@
 // one term at a time in ascending token order.  The result is bit-exact
 // against any implementation of that definition.
 //
-// Four kernels:
-//   match_logits -- the causal logit matrix S of each head, one wave per
-//                   64x64 tile, 8x8 independent FMA chains per lane over Q
-//                   and K slices staged in LDS as fp32 (one LDS byte read per
-//                   FMA), and each row's maximum over the tile;
-//   match_rowsum -- one thread per pair of rows (u, w-1-u) of every head, so
-//                   that the lanes of a wave do equal work: each row's max
-//                   from the tile maxima and its sum Z_u, v ascending;
-//   match_scores -- one workgroup per head, one thread per token: the column
-//                   sum F_v, u ascending (a wave's lanes read each row of S
-//                   together), then the TopK set by counting, for each token,
-//                   the tokens ranked above it;
-//   match_map    -- one wave per large head: Jaccard ratios against every
-//                   small head from TopK bitsets (popcounts), the argmax by
-//                   exact cross-multiplication, ties to the lowest small head.
+// Two kernels:
+//   match_heads -- one workgroup per head.  The window's query rows are walked
+//                  kRows at a time, so that the whole of Eq. 1 stays in the
+//                  workgroup: the rows' logits on the matrix cores into LDS,
+//                  each row's maximum and exponentials, its sum Z_u (v
+//                  ascending), and every column's sum F_v (one thread per
+//                  token, u ascending over the row blocks) in a register;
+//                  then the TopK set by counting, for each token, the tokens
+//                  ranked above it;
+//   match_map   -- one wave per large head: Jaccard ratios against every
+//                  small head from TopK bitsets (popcounts), the argmax by
+//                  exact cross-multiplication, ties to the lowest small head.
+//
+// The logits are fp32 FMA chains, and v_mfma_f32_16x16x1 (K = 1: one product
+// per element and instruction) is exactly one step of 16 x 64 of them: D =
+// fma(A, B, C) with one rounding, subnormals, infinities and NaN included
+// (compared bit for bit with the vector FMA over arbitrary bit patterns).  It
+// runs at 140-150 TFLOP/s here against 75 for plain vector FMAs.
 #include "common.h"
 #include "launch.h"
 
@@ -34,279 +37,379 @@
 namespace smallkv {
 namespace {
 
-constexpr int kTile = 64;     // tokens per side of a logit tile
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+
 constexpr int kMatchThreads = 256;
+constexpr int kWaves = kMatchThreads / kWave;
+constexpr int kXcd = 8;
+constexpr int kMaxWin = 256;          // tokens per window at most (one thread per token)
+constexpr int kStrip = 16;            // query rows per MFMA
+constexpr int kCols = 64;             // tokens per MFMA (4 blocks of 16)
+constexpr int kSlice = 32;            // head dims of the operands loaded at a time
+constexpr int kRows = 2 * kStrip;     // query rows per pass
 
-struct LogitArgs {
-  const void *q, *k;  // [B][layers][hq][w_cap][D], [B][layers][hkv][w_cap][D]
-  int layers, hq, hkv, w_cap, ld, nt;  // ld: row pitch of S
+struct HeadsArgs {
+  const void *q, *k;  // [B][layers][hq][w_cap][d], [B][layers][hkv][w_cap][d]
+  int layers, hq, hkv, d, heads, head0;  // heads of this model, the first one's index of H
   float scale;
-  const int32_t *win_len;
-  float *S;           // [B][H][w_cap][ld], entries v <= u < w written
-  float *pmax;        // [B][H][w_cap][nt]: max of row u over tile column V
-  int H, head0;       // heads per sequence (both models); this model's first
 };
 
-constexpr int kChunk = 32;            // head-dim slice staged per step
-constexpr int kPitch = kChunk + 4;    // LDS row pitch (floats)
-
-// Stage dims [c0, c0+kChunk) of 64 rows of one head's operand, from token r0,
-// into LDS as fp32; rows at or past the window are zero.  Every load of the
-// slice is issued before the first is used.
-// A 64-row x kChunk-dim slice in two steps: its 16-byte pieces into
-// registers (issued a chunk ahead of their use), then into LDS as fp32.
-template <typename T>
-struct Slice {
-  static constexpr int per = elem<T>::per16;
-  static constexpr int vpr = kChunk / per;       // 16-byte vectors per row slice
-  static constexpr int n = kTile * vpr / kWave;  // vectors per lane
-};
-
-template <typename T, int D>
-__device__ __forceinline__ void load_chunk(uint4 (&v)[Slice<T>::n], const T *src, int r0, int w, int c0) {
-  constexpr int per = Slice<T>::per, vpr = Slice<T>::vpr, n = Slice<T>::n;
-#pragma unroll
-  for (int q = 0; q < n; ++q) {
-    const int e = q * kWave + threadIdx.x, r = e / vpr, c = (e % vpr) * per;
-    v[q] = r0 + r < w ? *reinterpret_cast<const uint4 *>(src + (int64_t)(r0 + r) * D + c0 + c)
-                      : make_uint4(0u, 0u, 0u, 0u);
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ void store_chunk(float *dst, const uint4 (&v)[Slice<T>::n]) {
-  constexpr int per = Slice<T>::per, vpr = Slice<T>::vpr, n = Slice<T>::n;
-#pragma unroll
-  for (int q = 0; q < n; ++q) {
-    const int e = q * kWave + threadIdx.x, r = e / vpr, c = (e % vpr) * per;
-    float o[per];
-    elem<T>::unpack(v[q], o);
-#pragma unroll
-    for (int i = 0; i < per; i += 4)
-      *reinterpret_cast<float4 *>(dst + r * kPitch + c + i) =
-          make_float4(o[i], o[i + 1], o[i + 2], o[i + 3]);
-  }
-}
-
-// 8x8 FMA chains of one lane over one staged slice: rows ty + 8i of Qs,
-// columns tx + 8j of Ks, dims ascending.  kFull: all 64 rows and columns of
-// the tile are in the window (no bounds in the loop body).
-template <bool kFull>
-__device__ __forceinline__ void chains(float (&acc)[8][8], const float *Qs, const float *Ks, int ty,
-                                       int tx, int imax, int jmax) {
-#pragma unroll 1
-  for (int c = 0; c < kChunk; c += 4) {
-    float4 qa[8], kb[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (kFull || i < imax) qa[i] = *reinterpret_cast<const float4 *>(Qs + (ty + 8 * i) * kPitch + c);
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj)
-      if (kFull || jj < jmax) kb[jj] = *reinterpret_cast<const float4 *>(Ks + (tx + 8 * jj) * kPitch + c);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (!kFull && i >= imax) break;  // rows past the window (uniform)
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        if (!kFull && jj >= jmax) break;
-        float s = acc[i][jj];
-        s = __builtin_fmaf(qa[i].x, kb[jj].x, s);
-        s = __builtin_fmaf(qa[i].y, kb[jj].y, s);
-        s = __builtin_fmaf(qa[i].z, kb[jj].z, s);
-        s = __builtin_fmaf(qa[i].w, kb[jj].w, s);
-        acc[i][jj] = s;
-      }
-    }
-  }
-}
-
-// One wave per 64x64 tile (U, V) of the lower triangle.  Lane (ty, tx) owns
-// rows ty + 8i and columns tx + 8j (i, j < 8): 64 independent FMA chains,
-// each over the head dimension in ascending order.  kFull: the tile lies
-// wholly inside the window; otherwise it is in the window's last, partial
-// tile row, whose rows and columns past the window are skipped 8 at a time.
-template <typename T, int D, bool kFull>
-__device__ __forceinline__ void logits_tile(const LogitArgs &a, float *Qs, float *Ks, int U, int V,
-                                            int j, int b, int w) {
-  const int imax = min(8, (w - U * kTile + 7) / 8);
-  const int jmax = min(8, (w - V * kTile + 7) / 8);
-  const int layer = j / a.hq, h = j % a.hq, g = h / (a.hq / a.hkv);
-  const T *Q = static_cast<const T *>(a.q) + ((((int64_t)b * a.layers + layer) * a.hq + h) * a.w_cap) * D;
-  const T *K = static_cast<const T *>(a.k) + ((((int64_t)b * a.layers + layer) * a.hkv + g) * a.w_cap) * D;
-  const int lane = threadIdx.x, ty = lane >> 3, tx = lane & 7;
-  float acc[8][8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) acc[i][jj] = 0.0f;
-  uint4 qv[Slice<T>::n], kv[Slice<T>::n];
-  load_chunk<T, D>(qv, Q, U * kTile, w, 0);
-  load_chunk<T, D>(kv, K, V * kTile, w, 0);
-  for (int c0 = 0; c0 < D; c0 += kChunk) {
-    store_chunk<T>(Qs, qv);
-    store_chunk<T>(Ks, kv);
-    __syncthreads();
-    if (c0 + kChunk < D) {  // the next slice arrives while this one is used
-      load_chunk<T, D>(qv, Q, U * kTile, w, c0 + kChunk);
-      load_chunk<T, D>(kv, K, V * kTile, w, c0 + kChunk);
-    }
-    chains<kFull>(acc, Qs, Ks, ty, tx, imax, jmax);
-    __syncthreads();
-  }
-  const int64_t hrow = (int64_t)b * a.H + a.head0 + j;
-  float *S = a.S + hrow * a.w_cap * a.ld;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    if (i >= imax) continue;
-    const int u = U * kTile + ty + 8 * i;
-    float m = -INFINITY;
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      if (jj >= jmax) continue;
-      const int v = V * kTile + tx + 8 * jj;
-      float s = __fmul_rn(acc[i][jj], a.scale);
-      if (s == 0.0f) s = 0.0f;  // -0 -> +0
-      if (u < w && v <= u) {
-        S[(int64_t)u * a.ld + v] = s;
-        m = s > m ? s : m;
-      }
-    }
-    // max over the 8 lanes of this row group
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) {
-      const float x = __shfl_xor(m, o, kWave);
-      m = x > m ? x : m;
-    }
-    if (tx == 0 && u < w) a.pmax[(hrow * a.w_cap + u) * a.nt + V] = m;
-  }
-}
-
-// blockIdx.x < nt*(nt+1)/2 enumerates the lower triangle of tiles (those
-// wholly inside the window are computed); the next nt blocks are the tile
-// columns of the window's last tile row when the window is not a multiple of
-// 64 tokens.  Both kinds run in one launch.
-template <typename T, int D>
-__global__ __launch_bounds__(kWave) void match_logits(LogitArgs a) {
-  __shared__ float Qs[kTile * kPitch];
-  __shared__ float Ks[kTile * kPitch];
-  const int j = blockIdx.y, b = blockIdx.z;
-  const int w = clampi(a.win_len[b], 1, a.w_cap);
-  const int tri = a.nt * (a.nt + 1) / 2;
-  if ((int)blockIdx.x < tri) {
-    int U = 0;
-    while ((U + 1) * (U + 2) / 2 <= (int)blockIdx.x) ++U;
-    const int V = (int)blockIdx.x - U * (U + 1) / 2;
-    if ((U + 1) * kTile > w) return;
-    logits_tile<T, D, true>(a, Qs, Ks, U, V, j, b, w);
-  } else {
-    const int U = (w - 1) / kTile, V = (int)blockIdx.x - tri;
-    if ((U + 1) * kTile == w || V > U) return;
-    logits_tile<T, D, false>(a, Qs, Ks, U, V, j, b, w);
-  }
-}
-
-struct ScoreArgs {
-  const float *S, *pmax;
-  float2 *mz;               // [B][H][w_cap]: (m_u, Z_u)
-  int w_cap, ld, nt, H, nw; // nw: 64-token words per TopK bitset
+struct MatchArgs {
+  HeadsArgs m[2];           // the heads of this launch: m[0]'s, then m[1]'s (heads 0: none)
+  int w_cap, H, nw;         // nw: 64-token words per TopK bitset
   const int32_t *win_len, *top_k;
   uint64_t *bits;           // [B][H][nw]
   float *scores;            // optional [B][H][w_cap]
   uint64_t *top_bits;       // optional copy of bits
 };
 
-constexpr int kInFlight = 8;  // loads each thread issues before using them
+// Workgroups an XCD (x % 8) takes of n heads: consecutive ones, so that the
+// query heads of a kv head read its keys through one L2.
+__host__ __device__ constexpr int per_xcd(int n) { return (n + kXcd - 1) / kXcd; }
 
-// Row statistics: one thread per row u of every head (blockIdx.x covers 256
-// rows, blockIdx.y the head, blockIdx.z the sequence).  m_u from the tile
-// maxima; Z_u = e[u][0] + ... + e[u][u], one term at a time, v ascending.
-// Row u's max (from the tile maxima) and its sum Z_u, v ascending.
-__device__ __forceinline__ void row_sum(const ScoreArgs &a, int64_t hrow, int u) {
-  const float *pm = a.pmax + (hrow * a.w_cap + u) * a.nt;
-  float m = pm[0];
-  for (int V = 1; V <= u / kTile; ++V) m = pm[V] > m ? pm[V] : m;
-  const float4 *row = reinterpret_cast<const float4 *>(a.S + (hrow * a.w_cap + u) * a.ld);
-  const int n4 = u / 4 + 1;  // float4s holding v = 0 .. u
-  float z = 0.0f;
-  for (int i0 = 0; i0 < n4; i0 += kInFlight) {
-    float4 x[kInFlight];
+// The operands of one (16 query rows x 64 tokens) tile over kSlice dims, as
+// loaded: lane l holds dims 8*(l/16) .. +7 of query row l%16 (so block b of
+// the A operand holds dims 8b..) and all the slice's dims of token l.
+template <typename T>
+struct Raw {
+  static constexpr int per = elem<T>::per16;
+  uint4 q[kSlice / 4 / per], k[kSlice / per];
+};
+
+template <typename T>
+__device__ __forceinline__ void load_raw(Raw<T> &r, const T *Q, const T *K, int d, int w, int u0,
+                                         int v0, int c0) {
+  const int lane = threadIdx.x & (kWave - 1);
+  // rows past the window repeat its last one: their logits are not used
+  const T *q = Q + min(u0 + (lane & 15), w - 1) * d + c0 + (lane >> 4) * (kSlice / 4);
+  const T *k = K + min(v0 + lane, w - 1) * d + c0;
 #pragma unroll
-    for (int q = 0; q < kInFlight; ++q) x[q] = i0 + q < n4 ? row[i0 + q] : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int i = 0; i < kSlice / 4 / Raw<T>::per; ++i) r.q[i] = reinterpret_cast<const uint4 *>(q)[i];
 #pragma unroll
-    for (int q = 0; q < kInFlight; ++q) {
-      const int v = 4 * (i0 + q);
-      if (v <= u) z = __fadd_rn(z, cw_exp(__fsub_rn(x[q].x, m)));
-      if (v + 1 <= u) z = __fadd_rn(z, cw_exp(__fsub_rn(x[q].y, m)));
-      if (v + 2 <= u) z = __fadd_rn(z, cw_exp(__fsub_rn(x[q].z, m)));
-      if (v + 3 <= u) z = __fadd_rn(z, cw_exp(__fsub_rn(x[q].w, m)));
-    }
+  for (int i = 0; i < kSlice / Raw<T>::per; ++i) r.k[i] = reinterpret_cast<const uint4 *>(k)[i];
+}
+
+// One chain step of the tile for each dim of block BLK (8 dims), ascending.
+template <typename T, int BLK>
+__device__ __forceinline__ void chain8(f32x16_t &acc, const Raw<T> &r, const float (&a)[kSlice / 4]) {
+  constexpr int per = Raw<T>::per;
+#pragma unroll
+  for (int i = 0; i < 8 / per; ++i) {
+    float kv[per];
+    elem<T>::unpack(r.k[BLK * 8 / per + i], kv);
+#pragma unroll
+    for (int j = 0; j < per; ++j)
+      acc = __builtin_amdgcn_mfma_f32_16x16x1f32(a[i * per + j], kv[j], acc, 2, BLK, 0);
   }
-  a.mz[hrow * a.w_cap + u] = make_float2(m, z);
 }
 
-// Thread p sums rows p and w-1-p (once when they coincide), so that every
-// lane of a wave adds about w terms whatever its rows.
-__global__ __launch_bounds__(kMatchThreads) void match_rowsum(ScoreArgs a) {
-  const int p = blockIdx.x * kMatchThreads + threadIdx.x, head = blockIdx.y, b = blockIdx.z;
-  const int w = clampi(a.win_len[b], 1, a.w_cap);
-  if (p >= (w + 1) / 2) return;
-  const int64_t hrow = (int64_t)b * a.H + head;
-  row_sum(a, hrow, p);
-  if (w - 1 - p != p) row_sum(a, hrow, w - 1 - p);
+template <typename T>
+__device__ __forceinline__ void chain_slice(f32x16_t &acc, const Raw<T> &r) {
+  float a[kSlice / 4];
+#pragma unroll
+  for (int i = 0; i < kSlice / 4 / Raw<T>::per; ++i) elem<T>::unpack(r.q[i], a + i * Raw<T>::per);
+  chain8<T, 0>(acc, r, a);
+  chain8<T, 1>(acc, r, a);
+  chain8<T, 2>(acc, r, a);
+  chain8<T, 3>(acc, r, a);
 }
 
-// Column sums and the TopK set: one workgroup per head, thread v adds
-// e[u][v] / Z_u for u = v, v+1, ..., w-1, one term at a time (the threads of
-// a wave read one row of S together).
-__global__ __launch_bounds__(kMatchThreads) void match_scores(ScoreArgs a) {
-  __shared__ float2 smz[kMatchThreads];
-  __shared__ float sf[kMatchThreads];
-  const int head = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float x) {
+  return fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, false)));
+}
+
+// Maxima over the wave of eight values at once: halving exchanges hand every
+// eight lanes one of them, which they then reduce.  Value i's maximum ends in
+// lanes 8i .. 8i+7.
+__device__ __forceinline__ float wave_max8(float (&v)[8]) {
+  const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {  // lanes 0-31 keep values 0-3
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 4]), false, false);
+    v[i] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {  // even 16-lane rows keep the lower two
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 2]), false, false);
+    v[i] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  const bool upper = (lane & 8) != 0;
+  const float keep = upper ? v[1] : v[0], send = upper ? v[0] : v[1];
+  float x = fmaxf(keep, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(send), 0x128, 0xf, 0xf, false)));
+  x = dpp_max<0xB1>(x);     // lane ^ 1
+  x = dpp_max<0x4E>(x);     // lane ^ 2
+  return dpp_max<0x141>(x); // 8-lane mirror
+}
+
+// Exponentials, and with them Z and F, are held scaled by 2^64 (exact, as
+// none of them is ever subnormal or near overflow: e is 0 or 2^-116 .. 1), so
+// that no remainder of the divisions below is subnormal.
+constexpr float kUp = 0x1p64f, kDown = 0x1p-64f;
+
+// cw_exp(x) * 2^64, without a branch: x / ln 2 is rounded to an integer by
+// adding 1.5 * 2^23 (+ 64: even, so ties still go to even), whose low bits
+// then are the exponent to add to the polynomial's (0.7 .. 1.42).
+__device__ __forceinline__ float exp_up(float x) {
+  constexpr float kMagic = 0x1.8p23f + 64.0f;
+  const float t = __fadd_rn(__fmul_rn(x, 0x1.715476p+0f), kMagic);
+  const float k = __fsub_rn(t, kMagic);
+  float r = __builtin_fmaf(-k, 0x1.62e4p-1f, x);
+  r = __builtin_fmaf(-k, 0x1.7f7d1cp-20f, r);
+  float p = 0x1.a01a02p-13f;
+  p = __builtin_fmaf(p, r, 0x1.6c16c2p-10f);
+  p = __builtin_fmaf(p, r, 0x1.111112p-7f);
+  p = __builtin_fmaf(p, r, 0x1.555556p-5f);
+  p = __builtin_fmaf(p, r, 0x1.555556p-3f);
+  p = __builtin_fmaf(p, r, 0.5f);
+  p = __builtin_fmaf(p, r, 1.0f);
+  p = __builtin_fmaf(p, r, 1.0f);
+  const float e = __uint_as_float(__float_as_uint(p) + (__float_as_uint(t) << 23));
+  return x >= -80.0f ? e : 0.0f;
+}
+
+// e / Z correctly rounded, from 1 / Z in two parts (y its rounded value, dy the
+// rest): the quotient by both is within an ulp, and from there one correction
+// by its exact remainder rounds correctly (Markstein's theorem).  4
+// instructions against the 13 of a general division.  Z = 0 (y infinite, dy
+// NaN) gives NaN, as 0 / 0 does.
+struct Recip {
+  float z, y, dy;
+};
+__device__ __forceinline__ Recip recip(float z) {
+  Recip r;
+  r.z = z;
+  r.y = __fdiv_rn(1.0f, z);
+  r.dy = __fmul_rn(__builtin_fmaf(-r.y, z, 1.0f), r.y);
+  return r;
+}
+__device__ __forceinline__ float div_by(float e, const Recip &r) {
+  const float q = __builtin_fmaf(e, r.y, __fmul_rn(e, r.dy));
+  return __builtin_fmaf(__builtin_fmaf(-q, r.z, e), r.y, q);
+}
+
+// LDS of a workgroup (floats): the pass's logits [kRows][pitch], then Z and
+// its reciprocal per row.  The column sums take the logits' place at the end.  The pitch follows the window capacity, so that
+// five workgroups of 200-token windows fit a CU.
+__host__ __device__ constexpr int pitch_of(int w_cap) { return (w_cap + 3) / 4 * 4 + 4; }
+constexpr size_t heads_lds(int w_cap) {
+  const size_t f = (size_t)kRows * pitch_of(w_cap);
+  return ((f > kMaxWin ? f : kMaxWin) + 4 * kRows) * sizeof(float);
+}
+
+// Bound by the SIMDs' issue: fp32 MFMAs and vector instructions do not overlap
+// (measured side by side: their times add), and the window of the Qwen2 pair
+// (784 heads of d 128 and 336 of d 64, 200 tokens) has 106k cycles per SIMD of
+// the one (7.1 GFLOP of tiles for 4.9 of logits) and 90k of the other; the
+// rest is the passes' barriers, hidden by five workgroups per CU (three take
+// 164 us, two 207).  Whole matching 249 us with the logits in memory between
+// kernels and vector FMAs, 131 like this.
+template <typename T>
+__device__ __forceinline__ void head_scores(const MatchArgs &a, const HeadsArgs &m, float *lds,
+                                            int j, int b) {
+  const int pitch = pitch_of(a.w_cap);
+  float *const s = lds;
+  float4 *const zr = reinterpret_cast<float4 *>(lds + max(kRows * pitch, kMaxWin));
+  const int lane = threadIdx.x & (kWave - 1);
+  // the wave's part, shifted between workgroups: waves of one index share a
+  // SIMD, and the first parts have more of the tiles and columns (131 us
+  // against 135 without the shift on the 200-token Qwen2 pair; giving every
+  // wave the same number of tiles instead: 135)
+  const int part = (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + blockIdx.x / kXcd) & (kWaves - 1);
   const int w = clampi(a.win_len[b], 1, a.w_cap);
-  const int k = clampi(a.top_k[b], 1, w);
-  const int64_t hrow = (int64_t)b * a.H + head;
-  if (t < w) smz[t] = a.mz[hrow * a.w_cap + t];
-  __syncthreads();
+  const int layer = j / m.hq, h = j % m.hq, g = h / (m.hq / m.hkv);
+  const T *Q = static_cast<const T *>(m.q) + (((int64_t)b * m.layers + layer) * m.hq + h) * a.w_cap * m.d;
+  const T *K = static_cast<const T *>(m.k) + (((int64_t)b * m.layers + layer) * m.hkv + g) * a.w_cap * m.d;
+  const int64_t hrow = (int64_t)b * a.H + m.head0 + j;
+  const int c0 = part * kCols, col = c0 + lane;  // the wave's 64 columns of F
   float f = 0.0f;
-  if (t < w) {
-    const float *col = a.S + hrow * a.w_cap * a.ld + t;
-    // rows from the wave's first column, so that the lanes read each row together
-    for (int u0 = t & ~(kWave - 1); u0 < w; u0 += kInFlight) {
-      float x[kInFlight];
-#pragma unroll
-      for (int q = 0; q < kInFlight; ++q) {
-        const int u = u0 + q;
-        x[q] = (u < w && u >= t) ? col[(int64_t)u * a.ld] : 0.0f;
+  // tiles of the pass from row r0: 64-token chunks of one strip, then of the next
+  auto chunks = [&](int r0) { return (min(r0 + kRows, w) + kCols - 1) / kCols; };
+  auto tiles_of = [&](int r0) { return w - r0 > kStrip ? 2 * chunks(r0) : chunks(r0); };
+  auto load_tile = [&](Raw<T> &r, int r0, int tile, int c) {
+    const int nch = chunks(r0), strip = tile >= nch ? 1 : 0;
+    load_raw<T>(r, Q, K, m.d, w, r0 + strip * kStrip, (tile - strip * nch) * kCols, c);
+  };
+  auto load_first = [&](Raw<T> &r, int r0) {  // the wave's first tile of a pass
+    if (r0 < w && part < tiles_of(r0)) load_tile(r, r0, part, 0);
+  };
+  Raw<T> x, y;  // two slices: one in use, the next on its way
+  load_first(x, 0);
+  for (int r0 = 0; r0 < w; r0 += kRows) {
+    const int nr = min(kRows, w - r0);
+    // ---- logits: (16 rows x 64 tokens) tiles, one at a time per wave ------
+    const int nch = chunks(r0), tiles = tiles_of(r0);
+    for (int tile = part; tile < tiles; tile += kWaves) {
+      f32x16_t acc = {};
+      for (int c = 0; c < m.d; c += 2 * kSlice) {
+        load_tile(y, r0, tile, c + kSlice);
+        chain_slice<T>(acc, x);
+        if (c + 2 * kSlice < m.d) load_tile(x, r0, tile, c + 2 * kSlice);
+        else if (tile + kWaves < tiles) load_tile(x, r0, tile + kWaves, 0);
+        else load_first(x, r0 + kRows);
+        chain_slice<T>(acc, y);
       }
+      // lane l: rows 4(l/16) + r, tokens 16 blk + l%16 of the tile (tokens past
+      // the row's pitch go to its last, unused column)
+      const int strip = tile >= nch ? 1 : 0, v0 = (tile - strip * nch) * kCols;
+      const int row0 = strip * kStrip + (lane >> 4) * 4, vl = v0 + (lane & 15);
+      float *const srow = s + row0 * pitch;
 #pragma unroll
-      for (int q = 0; q < kInFlight; ++q) {
-        const int u = u0 + q;
-        if (u < w && u >= t) {
-          const float2 mz = smz[u];
-          f = __fadd_rn(f, __fdiv_rn(cw_exp(__fsub_rn(x[q], mz.x)), mz.y));
+      for (int blk = 0; blk < 4; ++blk) {
+        float *const p = srow + min(vl + blk * 16, pitch - 1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          p[r * pitch] = __builtin_fmaf(acc[4 * blk + r], m.scale, 0.0f);  // (a zero's sign is not used)
+      }
+    }
+    if (part >= tiles) load_first(x, r0 + kRows);
+    __syncthreads();
+    // ---- row maxima, then exponentials in place; 0 past the diagonal (adds
+    // nothing to Z)
+    constexpr int kOwn = kRows / kWaves;
+    const int own = part * kOwn;
+    if (own < nr) {  // the wave's rows (past nr: old values, not used)
+      float e[kOwn], mx[kOwn];
+      auto chunk = [&](int ch) {
+        const float *p = s + own * pitch + min(ch * kCols + lane, pitch - 1);
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) e[i] = p[i * pitch];
+        if (ch * kCols + kCols > r0 + 1) {  // (uniform) the chunk meets the diagonal
+          const int lim = r0 + own - ch * kCols - lane;
+#pragma unroll
+          for (int i = 0; i < kOwn; ++i) e[i] = lim + i >= 0 ? e[i] : -INFINITY;
+        }
+      };
+#pragma unroll
+      for (int i = 0; i < kOwn; ++i) mx[i] = -INFINITY;
+#pragma unroll 1
+      for (int ch = 0; ch < nch; ++ch) {
+        chunk(ch);
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) mx[i] = fmaxf(mx[i], e[i]);
+      }
+      static_assert(kOwn == 8, "wave_max8");
+      const float red = wave_max8(mx);
+#pragma unroll
+      for (int i = 0; i < kOwn; ++i)
+        mx[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(red), 8 * i));
+#pragma unroll 1
+      for (int ch = 0; ch < nch; ++ch) {
+        chunk(ch);
+        float *p = s + own * pitch + min(ch * kCols + lane, pitch - 1);
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) p[i * pitch] = exp_up(__fsub_rn(e[i], mx[i]));
+      }
+    }
+    __syncthreads();
+    // ---- Z_u: one thread per row, v ascending -------------------------------
+    if (part == kWaves - 1 && lane < nr) {
+      float z = 0.0f;
+      const float4 *row = reinterpret_cast<const float4 *>(s + lane * pitch);
+      const int n4 = (r0 + nr + 3) / 4;
+      auto add4 = [&](const float4 &e) {
+        z = __fadd_rn(z, e.x);
+        z = __fadd_rn(z, e.y);
+        z = __fadd_rn(z, e.z);
+        z = __fadd_rn(z, e.w);
+      };
+      int i = 0;
+      for (; i + 4 <= n4; i += 4) {  // four reads in flight
+        const float4 e0 = row[i], e1 = row[i + 1], e2 = row[i + 2], e3 = row[i + 3];
+        add4(e0);
+        add4(e1);
+        add4(e2);
+        add4(e3);
+      }
+      for (; i < n4; ++i) add4(row[i]);
+      const Recip r = recip(z * kDown);
+      zr[lane] = make_float4(r.z, r.y, r.dy, 0.0f);
+    }
+    __syncthreads();
+    // ---- F_v: one thread per token, u ascending ---------------------------
+    if (c0 < r0 + nr && col < w) {
+      constexpr int kBatch = 8;
+      const bool below = c0 + kCols <= r0 + 1;  // (uniform) the columns are below every row
+      const float *scol = s + col;
+      for (int i = 0; i < nr; i += kBatch) {  // rows past nr hold old values and are not added
+        float p[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+          const float4 z = zr[i + q];
+          p[q] = div_by(scol[(i + q) * pitch], Recip{z.x, z.y, z.z});
+        }
+        if (below && i + kBatch <= nr) {
+#pragma unroll
+          for (int q = 0; q < kBatch; ++q) f = __fadd_rn(f, p[q]);
+        } else {
+#pragma unroll
+          for (int q = 0; q < kBatch; ++q)
+            if (i + q < nr && col <= r0 + i + q) f = __fadd_rn(f, p[q]);
         }
       }
     }
-    sf[t] = f;
+    __syncthreads();  // before the next pass writes its logits
   }
+  f *= kDown;
+  s[col] = f;
   __syncthreads();
-  // TopK: ranked first by larger F, then by lower token index
-  bool in = false;
-  if (t < w) {
-    int above = 0;
-    for (int u = 0; u < w; ++u) {
-      const float x = sf[u];
-      above += (x > f || (x == f && u < t)) ? 1 : 0;
+  if (a.scores && col < w) a.scores[hrow * a.w_cap + col] = f;
+  // ---- TopK: ranked first by larger F, then by lower token index ----------
+  // One wave holds all the sums (their bits order as they do) and finds the
+  // k-th largest bit by bit; a NaN (of infinite logits) ranks above nothing
+  // and below nothing, and so is in.
+  if (part != 0) return;
+  constexpr int kWords = kMaxWin / kWave;
+  const int k = clampi(a.top_k[b], 1, w);
+  uint32_t key[kWords];
+  uint64_t valid[kWords];
+#pragma unroll
+  for (int c = 0; c < kWords; ++c) {
+    const float x = s[c * kWave + lane];
+    valid[c] = __builtin_amdgcn_ballot_w64(c * kWave + lane < w && x == x);
+    key[c] = __builtin_amdgcn_inverse_ballot_w64(valid[c]) ? __float_as_uint(x) : 0u;
+  }
+  uint32_t kth = 0;
+  for (uint32_t bit = 1u << 30; bit; bit >>= 1) {
+    const uint32_t cand = kth | bit;
+    int n = 0;
+#pragma unroll
+    for (int c = 0; c < kWords; ++c) n += __popcll(__builtin_amdgcn_ballot_w64(key[c] >= cand));
+    if (n >= k) kth = cand;
+    if (n == k) break;
+  }
+  int need = k, before = 0;  // ties taken, from the lowest token on
+#pragma unroll
+  for (int c = 0; c < kWords; ++c) need -= __popcll(__builtin_amdgcn_ballot_w64(key[c] > kth));
+#pragma unroll
+  for (int c = 0; c < kWords; ++c) {
+    const uint64_t ties = __builtin_amdgcn_ballot_w64(key[c] == kth) & valid[c];
+    const int rank = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(ties >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)ties, 0));
+    const uint64_t word = __builtin_amdgcn_ballot_w64(key[c] > kth) |
+                          (ties & __builtin_amdgcn_ballot_w64(rank < need)) |
+                          (__builtin_amdgcn_ballot_w64(c * kWave + lane < w) & ~valid[c]);
+    if (lane == 0 && c < a.nw) {
+      a.bits[hrow * a.nw + c] = word;
+      if (a.top_bits) a.top_bits[hrow * a.nw + c] = word;
     }
-    in = above < k;
+    before += __popcll(ties);
   }
-  const uint64_t word = __ballot(in);
-  const int wv = t / kWave;
-  if ((t & (kWave - 1)) == 0 && wv < a.nw) {
-    a.bits[hrow * a.nw + wv] = word;
-    if (a.top_bits) a.top_bits[hrow * a.nw + wv] = word;
-  }
-  if (a.scores && t < w) a.scores[hrow * a.w_cap + t] = f;
+}
+
+// blockIdx.x: a head of either model, m[0]'s (the larger ones) first: the
+// launch's last workgroups are its shortest; blockIdx.y: the sequence.
+template <typename T>
+__global__ __launch_bounds__(kMatchThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 5)))
+void match_heads(MatchArgs a) {
+  extern __shared__ __align__(16) float lds[];
+  const int xcd = blockIdx.x % kXcd, y = blockIdx.x / kXcd;
+  const int n0 = per_xcd(a.m[0].heads), n1 = per_xcd(a.m[1].heads);
+  const int mi = y >= n0 ? 1 : 0;
+  const HeadsArgs &m = a.m[mi];
+  const int j = mi ? xcd * n1 + (y - n0) : xcd * n0 + y;
+  if (j >= m.heads) return;  // (padding)
+  head_scores<T>(a, m, lds, j, blockIdx.y);
 }
 
 struct MapArgs {
@@ -361,38 +464,28 @@ __global__ __launch_bounds__(kMatchThreads) void match_map(MapArgs a) {
   if (lane == 0) a.head_map[(int64_t)b * a.nl + i] = bj;
 }
 
-template <typename T, int D>
-hipError_t launch_logits_t(const LogitArgs &la, int tiles, int heads, int batch, hipStream_t st) {
-  hipLaunchKernelGGL((match_logits<T, D>), dim3(tiles + la.nt, heads, batch), dim3(kWave), 0, st, la);
-  return hipGetLastError();
+HeadsArgs heads_of(const smallkv_window_t &m, int head0) {
+  HeadsArgs h{};
+  h.q = m.q;
+  h.k = m.k;
+  h.layers = m.n_layers;
+  h.hq = m.n_q_heads;
+  h.hkv = m.n_kv_heads;
+  h.d = m.head_dim;
+  h.heads = m.n_layers * m.n_q_heads;
+  h.head0 = head0;
+  h.scale = m.scale;
+  return h;
 }
 
-hipError_t launch_logits(const smallkv_window_t &m, int batch, int w_cap, const int32_t *win_len,
-                         float *S, float *pmax, int H, int head0, hipStream_t st) {
-  LogitArgs la{};
-  la.q = m.q;
-  la.k = m.k;
-  la.layers = m.n_layers;
-  la.hq = m.n_q_heads;
-  la.hkv = m.n_kv_heads;
-  la.w_cap = w_cap;
-  la.scale = m.scale;
-  la.win_len = win_len;
-  const int nt = (w_cap + kTile - 1) / kTile;
-  la.nt = nt;
-  la.ld = (w_cap + 3) / 4 * 4;
-  la.S = S;
-  la.pmax = pmax;
-  la.H = H;
-  la.head0 = head0;
-  const int tiles = nt * (nt + 1) / 2;
-  const int heads = m.n_layers * m.n_q_heads;
-  const bool bf = m.dtype == SMALLKV_BF16;
-  if (m.head_dim == 64)
-    return bf ? launch_logits_t<bf16_t, 64>(la, tiles, heads, batch, st)
-              : launch_logits_t<float, 64>(la, tiles, heads, batch, st);
-  return bf ? launch_logits_t<bf16_t, 128>(la, tiles, heads, batch, st)
-            : launch_logits_t<float, 128>(la, tiles, heads, batch, st);
+hipError_t launch_heads(const MatchArgs &a, int batch, bool f32, hipStream_t st) {
+  const dim3 grid(kXcd * (per_xcd(a.m[0].heads) + per_xcd(a.m[1].heads)), batch);
+  const size_t lds = heads_lds(a.w_cap);
+  if (f32)
+    hipLaunchKernelGGL((match_heads<float>), grid, dim3(kMatchThreads), lds, st, a);
+  else
+    hipLaunchKernelGGL((match_heads<bf16_t>), grid, dim3(kMatchThreads), lds, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -402,41 +495,42 @@ MatchLayout match_layout(const smallkv_match_t &m) {
   const int64_t H = (int64_t)m.large.n_layers * m.large.n_q_heads +
                     (int64_t)m.small.n_layers * m.small.n_q_heads;
   l.nw = (m.w_cap + kWave - 1) / kWave;
-  l.nt = (m.w_cap + kTile - 1) / kTile;
-  l.ld = (m.w_cap + 3) / 4 * 4;
+  // the size the header states: the logits stay in LDS, only the bitsets at
+  // the start are used
   auto round256 = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t mat = (size_t)m.batch * H * m.w_cap * l.ld * sizeof(float);
-  l.pmax_offset = round256(mat);
-  l.mz_offset = l.pmax_offset + round256((size_t)m.batch * H * m.w_cap * l.nt * sizeof(float));
-  l.bits_offset = l.mz_offset + round256((size_t)m.batch * H * m.w_cap * sizeof(float2));
-  l.total = l.bits_offset + (size_t)m.batch * H * l.nw * sizeof(uint64_t);
+  const size_t rows = (size_t)m.batch * H * m.w_cap, ld = (m.w_cap + 3) / 4 * 4, nt = l.nw;
+  l.total = round256(rows * ld * sizeof(float)) + round256(rows * nt * sizeof(float)) +
+            round256(rows * sizeof(float2)) + (size_t)m.batch * H * l.nw * sizeof(uint64_t);
   return l;
 }
 
 hipError_t launch_match(const smallkv_match_t &m, void *ws, hipStream_t st) {
-  const MatchLayout lay = match_layout(m);
-  char *base = static_cast<char *>(ws);
-  float *S = reinterpret_cast<float *>(base);
-  float *pmax = reinterpret_cast<float *>(base + lay.pmax_offset);
-  float2 *mz = reinterpret_cast<float2 *>(base + lay.mz_offset);
-  uint64_t *bits = reinterpret_cast<uint64_t *>(base + lay.bits_offset);
+  uint64_t *bits = static_cast<uint64_t *>(ws);
   const int nl = m.large.n_layers * m.large.n_q_heads;
   const int ns = m.small.n_layers * m.small.n_q_heads;
-  const int H = nl + ns;
-  hipError_t e = launch_logits(m.large, m.batch, m.w_cap, m.win_len, S, pmax, H, 0, st);
+  MatchArgs a{};
+  a.w_cap = m.w_cap;
+  a.H = nl + ns;
+  a.nw = match_layout(m).nw;
+  a.win_len = m.win_len;
+  a.top_k = m.top_k;
+  a.bits = bits;
+  a.scores = m.scores;
+  a.top_bits = m.top_bits;
+  a.m[0] = heads_of(m.large, 0);
+  hipError_t e;
+  if (m.small.dtype == m.large.dtype) {  // both models in one launch
+    a.m[1] = heads_of(m.small, nl);
+    e = launch_heads(a, m.batch, m.large.dtype == SMALLKV_F32, st);
+  } else {
+    e = launch_heads(a, m.batch, m.large.dtype == SMALLKV_F32, st);
+    if (e != hipSuccess) return e;
+    a.m[0] = heads_of(m.small, nl);
+    e = launch_heads(a, m.batch, m.small.dtype == SMALLKV_F32, st);
+  }
   if (e != hipSuccess) return e;
-  e = launch_logits(m.small, m.batch, m.w_cap, m.win_len, S, pmax, H, nl, st);
-  if (e != hipSuccess) return e;
-  ScoreArgs sa{S, pmax, mz, m.w_cap, lay.ld, lay.nt, H, lay.nw, m.win_len, m.top_k, bits,
-               m.scores, m.top_bits};
-  hipLaunchKernelGGL(match_rowsum, dim3(((m.w_cap + 1) / 2 + kMatchThreads - 1) / kMatchThreads, H, m.batch),
-                     dim3(kMatchThreads), 0, st, sa);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(match_scores, dim3(H, m.batch), dim3(kMatchThreads), 0, st, sa);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  MapArgs ma{bits, H, nl, ns, lay.nw, m.head_map};
-  const int waves = kMatchThreads / kWave;
-  hipLaunchKernelGGL(match_map, dim3((nl + waves - 1) / waves, m.batch), dim3(kMatchThreads), 0, st,
+  MapArgs ma{bits, a.H, nl, ns, a.nw, m.head_map};
+  hipLaunchKernelGGL(match_map, dim3((nl + kWaves - 1) / kWaves, m.batch), dim3(kMatchThreads), 0, st,
                      ma);
   return hipGetLastError();
 }

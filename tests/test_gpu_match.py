@@ -89,6 +89,21 @@ def test_ragged_windows_bf16():
     check_match(x, "ragged windows 1/64/65/173 bf16")
 
 
+@pytest.mark.parametrize("l_dtype,s_dtype", [("f32", "f32"), ("bf16", "bf16"), ("f32", "bf16"),
+                                             ("bf16", "f32")])
+def test_window_edges(l_dtype, s_dtype):
+    # windows around the 16-row strips, the 32-row passes and the 64-token
+    # chunks; both models' types, alike (one launch) and different (two)
+    _, W, _, _ = lib_modules()
+    win = [15, 16, 17, 32, 33, 63, 96, 97, 129, 193, 254, 255]
+    x = W.match_inputs(with_batch(W.WORKLOADS[1], len(win), 200), 255, DEV, win_len=win)
+    for name, dt in (("l", l_dtype), ("s", s_dtype)):
+        if dt == "bf16":
+            for t in ("q", "k"):
+                x[f"{name}_{t}"] = x[f"{name}_{t}"].to(torch.bfloat16)
+    check_match(x, f"window edges, large {l_dtype}, small {s_dtype}")
+
+
 def test_qwen2_7b_0_5b_window_200():
     _, W, _, _ = lib_modules()
     x = W.match_inputs(W.WORKLOADS[2], 200, DEV)
