@@ -28,6 +28,7 @@
 #include <limits.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
@@ -97,7 +98,7 @@ struct GroupShared {
   int cur[2 * kMaxG];           // list cursors (first entry not yet consumed)
   int cend[2 * kMaxG];          // with list offsets: each list's end of the token range
   int mstart[kMaxG];            // M-list cursor at the window start
-  int wcnt[kGW][kMaxG];         // marginal entries per head in each wave's rows
+  uint4 wcnt[kGW];              // marginal entries per head in each wave's rows, a halfword each
   int64_t hrow[kMaxG];          // row of each head's lists: small head (b, j), or its group
   int64_t prow[kMaxG];          // row of each head's marg_prob and mass
   float ac[kMaxG], am[kMaxG];
@@ -153,6 +154,21 @@ __device__ __forceinline__ float sum_xor32(float x) {
 __device__ __forceinline__ float sum_xor16(float x) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Sum over the wave, in lane 63 (DPP: prefix sums inside 16-lane rows, whose
+// ends then go to the next rows; lanes without a source add 0).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v) {
+  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+  v = dpp_add<0x111, 0xf>(v);     // row_shr:1
+  v = dpp_add<0x112, 0xf>(v);     // row_shr:2
+  v = dpp_add<0x114, 0xf>(v);     // row_shr:4
+  v = dpp_add<0x118, 0xf>(v);     // row_shr:8
+  v = dpp_add<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
 }
 
 __device__ __forceinline__ uint4 load16(const unsigned char *p) { return *reinterpret_cast<const uint4 *>(p); }
@@ -331,37 +347,41 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(2))) void h
     // membership of the range's one window: each owned list's entries of
     // the range, kF per lane per round, all lists' loads in flight together
     // (before the queries and accumulators hold registers)
-    constexpr int kF = 8;
-    int c0[kLPW], ne[kLPW];
+    int c0[kLPW], ne[kLPW], most = 0;
 #pragma unroll
     for (int i = 0; i < kLPW; ++i) {
       const int L = wave + kGW * i;
-      c0[i] = lists[i].on ? sh.cur[L] : 0;
-      ne[i] = lists[i].on ? sh.cend[L] - c0[i] : 0;
+      c0[i] = lists[i].on ? __builtin_amdgcn_readfirstlane(sh.cur[L]) : 0;
+      ne[i] = lists[i].on ? __builtin_amdgcn_readfirstlane(sh.cend[L]) - c0[i] : 0;
+      most = max(most, ne[i]);
       if (lists[i].on && L >= g && lane == 0) sh.mstart[L - g] = c0[i];
     }
-    for (int k0 = 0;; k0 += kF * kWave) {
-      bool any = false;
+    // kF entries of each list per lane and round, as many as the range needs
+    // (a 512-token range: two)
+    auto rounds = [&](auto kf) {
+      constexpr int kF = decltype(kf)::value;
+      for (int k0 = 0; k0 < most; k0 += kF * kWave) {
+        int e[kLPW][kF];
 #pragma unroll
-      for (int i = 0; i < kLPW; ++i) any |= k0 < ne[i];
-      if (!any) break;
-      int e[kLPW][kF];
+        for (int i = 0; i < kLPW; ++i)
 #pragma unroll
-      for (int i = 0; i < kLPW; ++i)
+          for (int k = 0; k < kF; ++k) {
+            const int pos = k0 + lane + kWave * k;
+            e[i][k] = pos < ne[i] ? lists[i].p[c0[i] + pos] : -1;
+          }
 #pragma unroll
-        for (int k = 0; k < kF; ++k) {
-          const int pos = k0 + lane + kWave * k;
-          e[i][k] = pos < ne[i] ? lists[i].p[c0[i] + pos] : -1;
-        }
+        for (int i = 0; i < kLPW; ++i)
 #pragma unroll
-      for (int i = 0; i < kLPW; ++i)
-#pragma unroll
-        for (int k = 0; k < kF; ++k) {
-          // (an entry outside the window could come only from wrong offsets)
-          const int p = e[i][k] - t_begin;
-          if ((unsigned)p < (unsigned)(t_end - t_begin)) atomicOr(&sh.mem[p >> 1], lists[i].bit << (16 * (p & 1)));
-        }
-    }
+          for (int k = 0; k < kF; ++k) {
+            // (an entry outside the window could come only from wrong offsets)
+            const int p = e[i][k] - t_begin;
+            if ((unsigned)p < (unsigned)(t_end - t_begin)) atomicOr(&sh.mem[p >> 1], lists[i].bit << (16 * (p & 1)));
+          }
+      }
+    };
+    if (most <= 2 * kWave) rounds(std::integral_constant<int, 2>{});
+    else if (most <= 4 * kWave) rounds(std::integral_constant<int, 4>{});
+    else rounds(std::integral_constant<int, 8>{});
   }
 
   // the group's queries as the B operand of QK: lane holds head hc, dims 32ks + 8lq .. +7
@@ -448,66 +468,43 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(2))) void h
     __syncthreads();
 
     // ---- compaction into ascending union rows ---------------------------
-    // Thread t takes pc consecutive positions, so wave w's rows are those
-    // of positions [w * 64 * pc, (w + 1) * 64 * pc): it streams exactly the
-    // rows its own threads compact, and counts their marginal bits here.
-    // Thread t takes positions t*pc .. +pc-1: the membership words from
-    // word t*pc/2 on, shifted by half a word when t*pc is odd, so that
-    // mw[k] holds positions 2k and 2k+1 of the thread.
-    constexpr int PW = kWin / kGT / 2;  // most membership words per thread
+    // Wave w takes the 64-position rows p0 .. p0 + 64 pc, one position per
+    // lane: a row's members are a ballot, their places the running count plus
+    // an mbcnt, and it streams exactly the rows it compacts here (kept from
+    // uni[p0] on).  Its marginal entries per head, which place the next
+    // waves in the heads' weight lists, are summed a byte per head (at most
+    // 16 per lane), then across the lanes in halfwords: 16 ballots per head
+    // and a thread's run of positions instead of a row took 7800 cycles per
+    // 512-token range and 10100 per 2048.
     const int pc = (we - ws + kGT - 1) / kGT;
-    const int w0 = (tid * pc) >> 1, odd = (tid * pc) & 1;
-    // (loops over words and positions stop at the window's pc: wave-uniform)
-    uint32_t mw[PW];
-    if ((pc & 1) == 0) {  // every thread starts on a word boundary
-#pragma unroll
-      for (int k = 0; k < PW; ++k) mw[k] = 2 * k < pc ? sh.mem[w0 + k] : 0u;
-    } else {
-      uint32_t nx = 0u;
-#pragma unroll
-      for (int k = PW; k >= 0; --k) {
-        uint32_t x = 0u;
-        if (2 * k <= pc && 2 * k < pc + odd && w0 + k < kWin / 2) x = sh.mem[w0 + k];
-        if (k < PW) {
-          mw[k] = odd ? __builtin_amdgcn_alignbit(nx, x, 16) : x;
-          if (2 * k + 1 >= pc) mw[k] &= 2 * k < pc ? 0xffffu : 0u;  // past the thread's last position
-        }
-        nx = x;
-      }
-    }
-    int cnt = 0;
-#pragma unroll
-    for (int k = 0; k < PW; ++k) cnt += ((mw[k] & 0xffffu) != 0u) + ((mw[k] >> 16) != 0u);
-    int inc = cnt;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int y = __shfl_up(inc, o, kWave);
-      if (lane >= o) inc += y;
-    }
-    // each wave's union rows go to its own range of uni, from wave*64*pc on
     const int r0 = wave * kWave * pc;
-    const int r1 = r0 + __builtin_amdgcn_readlane(inc, kWave - 1);
-    for (int h = 0; h < g; ++h) {
-      int c = 0;
-#pragma unroll
-      for (int k = 0; k < PW; ++k) {
-        if (2 * k >= pc) break;
-        c += __popcll(__ballot((mw[k] >> (8 + h)) & 1u)) + __popcll(__ballot((mw[k] >> (24 + h)) & 1u));
-      }
-      if (lane == 0) sh.wcnt[wave][h] = c;
-    }
-    __syncthreads();  // every thread has read its words (a word may be shared by two): clear them
-#pragma unroll
-    for (int k = 0; k <= PW; ++k)
-      if (2 * k <= pc && 2 * k < pc + odd) sh.mem[w0 + k] = 0u;
+    int r1 = r0;
     {
-      int o = r0 + inc - cnt;
+      constexpr int kRows = kWin / kGT;  // most rows per wave
+      const uint16_t *const m16 = reinterpret_cast<const uint16_t *>(sh.mem) + r0 + lane;
+      uint32_t mb[kRows];
 #pragma unroll
-      for (int k = 0; k < 2 * PW; ++k) {
-        if (k >= pc) break;
-        const uint32_t m = (mw[k >> 1] >> (16 * (k & 1))) & 0xffffu;
-        if (m) sh.uni[o++] = (m << kPosBits) | (uint32_t)(tid * pc + k);
+      for (int i = 0; i < kRows; ++i) mb[i] = i < pc ? m16[i * kWave] : 0u;
+      uint32_t c0 = 0, c1 = 0;  // marginal entries of heads 0-3 and 4-7, a byte each
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) {
+        if (i >= pc) break;
+        const uint64_t nz = __builtin_amdgcn_ballot_w64(mb[i] != 0u);
+        const int at = r1 + __builtin_amdgcn_mbcnt_hi((uint32_t)(nz >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)nz, 0));
+        if (mb[i]) sh.uni[at] = (mb[i] << kPosBits) | (uint32_t)(r0 + i * kWave + lane);
+        r1 += __popcll(nz);
+        // four bits to the low bit of four bytes
+        c0 += (((mb[i] >> 8) & 15u) * 0x204081u) & 0x01010101u;
+        c1 += ((mb[i] >> 12) * 0x204081u) & 0x01010101u;
       }
+      // the wave's words are read: clear them for the next window (no other
+      // wave reads or sets them before the barrier that ends this one)
+      for (int i = lane; i < pc * (kWave / 2); i += kWave) sh.mem[(r0 >> 1) + i] = 0u;
+      uint32_t t[4] = {c0 & 0xff00ffu, (c0 >> 8) & 0xff00ffu, c1 & 0xff00ffu, (c1 >> 8) & 0xff00ffu};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t[i] = wave_total(t[i]);
+      if (lane == kWave - 1) sh.wcnt[wave] = make_uint4(t[0], t[1], t[2], t[3]);
     }
     if constexpr (resolved) {
       // this wave's own rows (written by its own threads above); the
@@ -537,18 +534,28 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(2))) void h
       wave_lds_fence();
     }
     // element index in marg_prob of the next marginal entry of each head
-    // (wave-uniform: kept in SGPRs)
-    int mpos[kMaxG];
-#pragma unroll
-    for (int h = 0; h < kMaxG; ++h) {
-      int p = 0;
-      if (h < g) {
-        p = (int)(sh.prow[h] * a.km_cap) + sh.mstart[h];
-        for (int w = 0; w < wave; ++w) p += sh.wcnt[w][h];
-      }
-      mpos[h] = __builtin_amdgcn_readfirstlane(p);
-    }
+    // (wave-uniform: kept in SGPRs): its list's entry at the window's start
+    // and what the waves before this one hold
+    const int hl = lane & (kMaxG - 1);
+    const int list = hl < g ? (int)(sh.prow[hl] * a.km_cap) + sh.mstart[hl] : 0;
     __syncthreads();
+    int mpos[kMaxG];
+    {
+      uint4 before = make_uint4(0u, 0u, 0u, 0u);
+      for (int w = 0; w < wave; ++w) {
+        const uint4 v = sh.wcnt[w];
+        before.x += v.x;
+        before.y += v.y;
+        before.z += v.z;
+        before.w += v.w;
+      }
+      // heads 0 and 2 in x, 1 and 3 in y, 4 and 6 in z, 5 and 7 in w
+      const uint32_t lo = (hl & 1) ? before.y : before.x, hi = (hl & 1) ? before.w : before.z;
+      const uint32_t pair = hl < 4 ? lo : hi;
+      const int start = list + (int)((hl & 2) ? pair >> 16 : pair & 0xffffu);
+#pragma unroll
+      for (int h = 0; h < kMaxG; ++h) mpos[h] = __builtin_amdgcn_readlane(start, h);
+    }
 
     // ---- stream the rows: QK, online softmax, P.V -----------------------
     // Software pipeline: the next block's K rows and marginal weights are
