@@ -7,18 +7,23 @@
 // partial record per query head of the GQA group: (chunk max, sum, P.V).
 //
 // bf16 kernel (small_attn_mfma), per tile:
-//   * K rows are staged in LDS with coalesced 16-byte loads; the V rows of
-//     the tile are loaded into registers at the same time, 8 consecutive
-//     tokens x 8 dims per thread, so their latency hides behind QK;
-//   * each thread owns one token and evaluates the logit of every query head
-//     of the group as a sequential fp32 FMA chain over the head dimension
-//     (the bit-exact ranking key), and writes it out;
-//   * P = exp(s - running max) is split into bf16 hi + lo parts and V is
-//     transposed in registers (v_perm) into a token-contiguous LDS tile, so
-//     P.V runs on MFMA (v_mfma_f32_16x16x32_bf16): M = query heads (padded
-//     to 16), N = 16 dims per wave, K = 32 tokens per instruction, twice
-//     (hi, lo), which keeps ~16 bits of P.
-// fp32 kernel (small_attn_valu): the same tiling with P.V on fp32 FMA.
+//   * K rows are staged in LDS with coalesced 16-byte loads; with several tiles
+//     per chunk the next tile's K rows travel in registers meanwhile;
+//   * each lane owns one token, and the logits of every query head of the
+//     group are sequential fp32 FMA chains over the head dimension (the
+//     bit-exact ranking key), run on the matrix cores (see QTile) and written
+//     out.  Vector FMAs with the queries in scalar registers, whose loads
+//     return out of order and so had to be waited for one step at a time,
+//     took 32.2 us for stage 1 of the Qwen2-7B step against 28.7, 486 against
+//     447 on the ragged batch, 14.4 against 12 on a 1237-token step;
+//   * P = exp(s - running max) is split into bf16 hi + lo parts and V (8
+//     consecutive tokens x 8 dims per thread) is transposed in registers
+//     (v_perm) into a token-contiguous LDS tile, so P.V runs on MFMA
+//     (v_mfma_f32_16x16x32_bf16): M = query heads (padded to 16), N = 16 dims
+//     per wave, K = 32 tokens per instruction, twice (hi, lo), which keeps ~16
+//     bits of P.
+// fp32 kernel (small_attn_valu): the same tiling and logits with P.V on fp32
+// FMA.
 // small_attn_merge: log-sum-exp combine of a head's chunk records.
 #include "common.h"
 #include "launch.h"
@@ -68,33 +73,71 @@ __device__ __forceinline__ bool unit_pos(const SmallArgs &a, UnitPos &u) {
   return u.t0 < u.n;
 }
 
-// Sequential fp32 FMA chain over the head dimension, then one multiply by
-// the scale; -0 becomes +0.  This is the bit-exact ranking key.
-template <int D>
-__device__ __forceinline__ float chain_logit(const float *q, const float *k, float scale) {
-  float acc = 0.0f;
+// The logits, sequential fp32 FMA chains over the head dimension from +0 (then
+// one multiply by the scale, -0 to +0): the bit-exact ranking key.  They run
+// on the matrix cores: v_mfma_f32_4x4x1 (K = 1) forms one
+// product per element and adds it with one rounding, so each instruction is
+// exactly one step of 4 heads x 64 tokens' chains (bit for bit the vector FMA,
+// subnormals, infinities and NaN included).  The tokens sit one per lane in the
+// B operand, the logits one per lane and head in the result; the A operand
+// holds 16 dims of four heads (lane l: head l % 4, dim l / 4 of the 16), and
+// each instruction broadcasts one dim's block to all.
+template <int D, int GP>
+struct QTile {
+  float a[GP / 4][D / 16];
+  // Q: [g][D] of the group; heads at or past g are zero
+  template <typename T>
+  __device__ __forceinline__ void load(const void *q, int64_t head0, int g) {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int c = 0; c < D; ++c) acc = __builtin_fmaf(q[c], k[c], acc);
-  const float s = acc * scale;
-  return s == 0.0f ? 0.0f : s;
-}
-
-// The same chain with q read as bf16 pairs through the constant address
-// space: wave-uniform scalar loads, so every FMA takes q from an SGPR and the
-// query costs no LDS traffic.  Bit-identical to chain_logit.
-typedef const __attribute__((address_space(4))) uint32_t *const_u32_ptr;
-template <int D>
-__device__ __forceinline__ float chain_logit_sq(const_u32_ptr qw, const float *k, float scale) {
-  float acc = 0.0f;
+    for (int hg = 0; hg < GP / 4; ++hg)
 #pragma unroll
-  for (int c = 0; c < D; c += 2) {
-    const uint32_t w = qw[c / 2];
-    acc = __builtin_fmaf(bf16_lo(w), k[c], acc);
-    acc = __builtin_fmaf(bf16_hi(w), k[c + 1], acc);
+      for (int j = 0; j < D / 16; ++j) {
+        const int h = hg * 4 + (lane & 3);
+        a[hg][j] = h < g ? elem<T>::load1(q, (head0 + h) * D + j * 16 + (lane >> 2)) : 0.0f;
+      }
   }
-  const float s = acc * scale;
-  return s == 0.0f ? 0.0f : s;
-}
+  // one step for dim 16 J + C of every head
+  template <int J, int C>
+  __device__ __forceinline__ void step(f32x4_t (&s)[GP / 4], float k) const {
+#pragma unroll
+    for (int hg = 0; hg < GP / 4; ++hg)
+      s[hg] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[hg][J], k, s[hg], 4, C, 0);
+  }
+  // dims 16 J .. +15, ascending
+  template <int J>
+  __device__ __forceinline__ void steps16(f32x4_t (&s)[GP / 4], const float (&k)[16]) const {
+    step<J, 0>(s, k[0]);
+    step<J, 1>(s, k[1]);
+    step<J, 2>(s, k[2]);
+    step<J, 3>(s, k[3]);
+    step<J, 4>(s, k[4]);
+    step<J, 5>(s, k[5]);
+    step<J, 6>(s, k[6]);
+    step<J, 7>(s, k[7]);
+    step<J, 8>(s, k[8]);
+    step<J, 9>(s, k[9]);
+    step<J, 10>(s, k[10]);
+    step<J, 11>(s, k[11]);
+    step<J, 12>(s, k[12]);
+    step<J, 13>(s, k[13]);
+    step<J, 14>(s, k[14]);
+    step<J, 15>(s, k[15]);
+  }
+  // the whole chains over the K row at `row` (D elements of T, in LDS)
+  template <typename T, int J = 0>
+  __device__ __forceinline__ void chains(f32x4_t (&s)[GP / 4], const unsigned char *row) const {
+    if constexpr (J < D / 16) {
+      float k[16];
+#pragma unroll
+      for (int w = 0; w < 16 / elem<T>::per16; ++w)
+        elem<T>::unpack(*reinterpret_cast<const uint4 *>(row + J * 16 * (int)sizeof(T) + w * 16),
+                        k + w * elem<T>::per16);
+      steps16<J>(s, k);
+      chains<T, J + 1>(s, row);
+    }
+  }
+};
 
 // Max (or sum) over the wave of GP per-head values at once.  Halving
 // exchanges hand every lane group one head (head = lane >> (6 - log2 GP)):
@@ -196,8 +239,11 @@ __device__ __forceinline__ void stage_k(unsigned char *tile, const unsigned char
 // kPre: the chunk has several tiles; the next tile's K rows travel into
 // registers while this tile computes (costs registers, so single-tile chunks
 // go without).
+// Groups of 5 to 8 heads of d 64 are held to 168 registers, so that three
+// workgroups share a CU (ragged batch stage 1 462 -> 447 us).
 template <int D, int GP, int G, bool kPre>
-__global__ __launch_bounds__(kThreads) void small_attn_mfma(SmallArgs a) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 64 && GP == 8 ? 3 : 1)))
+void small_attn_mfma(SmallArgs a) {
   using C = SmallCfg<bf16_t, D>;
   constexpr int TILE = C::TILE;
   constexpr int DC = D / 8;                   // 8-dim chunks per row
@@ -217,10 +263,12 @@ __global__ __launch_bounds__(kThreads) void small_attn_mfma(SmallArgs a) {
   __shared__ float salpha[16];
 
   UnitPos u;
-  if (!unit_pos(a, u)) return;
+  const bool in = unit_pos(a, u);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = G > 0 ? G : a.g;
-  constexpr int GC = G > 0 ? G : GP;  // heads the chains run on
+  QTile<D, GP> qt;  // (requested before the sequence's length arrives)
+  qt.template load<bf16_t>(a.q, u.head0, g);
+  if (!in) return;
   const int64_t row0 = (int64_t)u.unit * a.n_cap;
   const unsigned char *kb = reinterpret_cast<const unsigned char *>(a.k) + row0 * C::ROWB;
   const unsigned char *vb = reinterpret_cast<const unsigned char *>(a.v) + row0 * C::ROWB;
@@ -238,7 +286,7 @@ __global__ __launch_bounds__(kThreads) void small_attn_mfma(SmallArgs a) {
   for (int nb = 0; nb < NBW; ++nb) acc[nb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
   constexpr int KR = C::TILE * C::V16 / kThreads;  // 16-byte K pieces per thread
-  uint4 kpre[kPre ? KR : 1];
+  uint4 kpre[KR];
   auto load_k = [&](int t, int n) {
 #pragma unroll
     for (int r = 0; r < KR; ++r) {
@@ -256,76 +304,39 @@ __global__ __launch_bounds__(kThreads) void small_attn_mfma(SmallArgs a) {
       *reinterpret_cast<uint4 *>(tile + row * C::ROWS + w * 16) = kpre[r];
     }
   };
-  if constexpr (kPre) {
-    load_k(u.t0, min(TILE, u.t1 - u.t0));
-    store_k();
-  }
+  uint4 vr[8];  // V rows of 8 consecutive tokens x one 8-dim chunk
+  auto load_v = [&](int t, int n) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int tok = tb8 * 8 + k;
+      vr[k] = tok < n ? stream16(vb + (int64_t)(t + tok) * C::ROWB + dc * 16)
+                      : make_uint4(0u, 0u, 0u, 0u);
+    }
+  };
+  // a chunk of one tile has its V rows on their way during QK as well (with
+  // several tiles that would cost the third workgroup per CU)
+  load_k(u.t0, min(TILE, u.t1 - u.t0));
+  if constexpr (!kPre) load_v(u.t0, min(TILE, u.t1 - u.t0));
+  store_k();
 
   for (int tb = u.t0; tb < u.t1; tb += TILE) {
     const int nr = min(TILE, u.t1 - tb);
     const int tn = tb + TILE;
-    if constexpr (kPre) {
-      __syncthreads();  // this tile's K is in LDS
+    __syncthreads();  // this tile's K is in LDS
+    if constexpr (kPre)
       if (tn < u.t1) load_k(tn, min(TILE, u.t1 - tn));
-    } else {
-      stage_k<bf16_t, D>(tile, kb + (int64_t)tb * C::ROWB, nr);
-      __syncthreads();
-    }
 
-    // ---- logits: one token per thread, sequential FMA chains ------------
-    // The chain of each head runs over dims 0..D-1 in order; the K row is
-    // unpacked half a row at a time to keep registers low.
+    // ---- logits: one token per lane (tid < TILE), all heads' chains ------
     float s[GP];
+    if (wave * kWave < nr) {  // (whole waves: lanes past nr run on rows not loaded)
+      f32x4_t sv[GP / 4];
 #pragma unroll
-    for (int i = 0; i < GP; ++i) s[i] = 0.0f;
-    if (tid < nr) {
-      const_u32_ptr qw = (const_u32_ptr)(reinterpret_cast<uintptr_t>(a.q)) + u.head0 * (D / 2);
-      // q of one (half, head) step: QW words in SGPRs.  Scalar loads return
-      // out of order, so any use of one waits for all in flight: each step
-      // first touches its own q (one FMA, which waits), then requests the
-      // next step's q, then runs the rest of its chain while those arrive.
-      constexpr int QW = D / 4;
-      constexpr int NSTEP = 2 * GC;
-      auto q_at = [&](int st) { return qw + (st % GC) * (D / 2) + (st / GC) * QW; };
-      uint32_t qc[QW], qn[QW];
-#pragma unroll
-      for (int w = 0; w < QW; ++w) qc[w] = q_at(0)[w];
-      float kr[D / 2];
-#pragma unroll
-      for (int st = 0; st < NSTEP; ++st) {
-        const int i = st % GC, half = st / GC;
-        if (G == 0 && i >= g) {  // padded head slot of a runtime group size
-          if (st + 1 < NSTEP)
-#pragma unroll
-            for (int w = 0; w < QW; ++w) qc[w] = q_at(st + 1)[w];
-          continue;
-        }
-        if (i == 0) {  // this half of the K row, unpacked
-#pragma unroll
-          for (int w = 0; w < C::V16 / 2; ++w) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(tile + tid * C::ROWS + (half * C::V16 / 2 + w) * 16);
-            elem<bf16_t>::unpack(v, kr + w * 8);
-          }
-        }
-        s[i] = __builtin_fmaf(bf16_lo(qc[0]), kr[0], s[i]);
-        __builtin_amdgcn_sched_barrier(0);
-        if (st + 1 < NSTEP)
-#pragma unroll
-          for (int w = 0; w < QW; ++w) qn[w] = q_at(st + 1)[w];
-        __builtin_amdgcn_sched_barrier(0);
-        s[i] = __builtin_fmaf(bf16_hi(qc[0]), kr[1], s[i]);
-#pragma unroll
-        for (int c = 2; c < D / 2; c += 2) {
-          s[i] = __builtin_fmaf(bf16_lo(qc[c / 2]), kr[c], s[i]);
-          s[i] = __builtin_fmaf(bf16_hi(qc[c / 2]), kr[c + 1], s[i]);
-        }
-#pragma unroll
-        for (int w = 0; w < QW; ++w) qc[w] = qn[w];
-      }
+      for (int hg = 0; hg < GP / 4; ++hg) sv[hg] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      qt.template chains<bf16_t>(sv, tile + tid * C::ROWS);
 #pragma unroll
       for (int i = 0; i < GP; ++i) {
-        if (i < g) {
-          float x = s[i] * a.scale;
+        if (i < g && tid < nr) {
+          float x = sv[i / 4][i % 4] * a.scale;
           x = x == 0.0f ? 0.0f : x;
           lrow[(int64_t)i * a.n_cap + tb + tid] = x;
           s[i] = x;
@@ -345,14 +356,7 @@ __global__ __launch_bounds__(kThreads) void small_attn_mfma(SmallArgs a) {
       constexpr int sh = head_shift<GP>();
       if ((lane & ((1 << sh) - 1)) == 0) red[wave * GP + (lane >> sh)] = mx;
     }
-    // V rows of 8 consecutive tokens x one 8-dim chunk, into registers
-    uint4 vr[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int tok = tb8 * 8 + k;
-      vr[k] = tok < nr ? stream16(vb + (int64_t)(tb + tok) * C::ROWB + dc * 16)
-                       : make_uint4(0u, 0u, 0u, 0u);
-    }
+    if constexpr (kPre) load_v(tb, nr);
     __syncthreads();  // K tile no longer read; red visible
 
     // ---- online softmax, P hi/lo and V^T into LDS -----------------------
@@ -456,18 +460,16 @@ __global__ __launch_bounds__(kThreads) void small_attn_valu(SmallArgs a) {
   constexpr int NDG = D / VD;        // dim groups
   constexpr int NTP = kThreads / NDG;  // token stripes
   __shared__ __align__(16) unsigned char tile[TILE * C::ROWS];
-  __shared__ __align__(16) float sq[GP * D];
   __shared__ __align__(16) float sp[TILE * GP];
   __shared__ float red[4 * GP];
 
   UnitPos u;
-  if (!unit_pos(a, u)) return;
+  const bool in = unit_pos(a, u);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = a.g;
-  for (int x = tid; x < GP * D; x += kThreads) {
-    const int i = x / D, c = x % D;
-    sq[x] = i < g ? elem<float>::load1(a.q, (u.head0 + i) * D + c) : 0.0f;
-  }
+  QTile<D, GP> qt;  // (requested before the sequence's length arrives)
+  qt.template load<float>(a.q, u.head0, g);
+  if (!in) return;
   const int64_t row0 = (int64_t)u.unit * a.n_cap;
   const unsigned char *kb = reinterpret_cast<const unsigned char *>(a.k) + row0 * C::ROWB;
   const unsigned char *vb = reinterpret_cast<const unsigned char *>(a.v) + row0 * C::ROWB;
@@ -489,17 +491,16 @@ __global__ __launch_bounds__(kThreads) void small_attn_valu(SmallArgs a) {
     float s[GP];
 #pragma unroll
     for (int i = 0; i < GP; ++i) s[i] = -INFINITY;
-    if (tid < nr) {
-      float kr[D];
+    if (wave * kWave < nr) {
+      f32x4_t sv[GP / 4];
 #pragma unroll
-      for (int w = 0; w < C::V16; ++w) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(tile + tid * C::ROWS + w * 16);
-        elem<float>::unpack(v, kr + w * 4);
-      }
+      for (int hg = 0; hg < GP / 4; ++hg) sv[hg] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      qt.template chains<float>(sv, tile + tid * C::ROWS);
 #pragma unroll
       for (int i = 0; i < GP; ++i)
-        if (i < g) {
-          s[i] = chain_logit<D>(sq + i * D, kr, a.scale);
+        if (i < g && tid < nr) {
+          const float x = sv[i / 4][i % 4] * a.scale;
+          s[i] = x == 0.0f ? 0.0f : x;
           lrow[(int64_t)i * a.n_cap + tb + tid] = s[i];
         }
     }
