@@ -19,13 +19,11 @@ constexpr int kMaxChunks = 4096;
 
 // Executed by a whole workgroup of NT threads (NT a multiple of 64 and of
 // the head dim d, which is 64 or 128).  Thread (c, grp) combines the records
-// s = grp, grp + NT/d, ... of output dim c online (one round trip of loads),
-// then the groups are combined through LDS.  lds_red: at least 3*NT + 2
-// floats.  Returns M and Z to every thread and hands out[c] = O_c / Z to
-// `store` (called by threads c < d).
-template <int NT, typename Store>
-__device__ __forceinline__ void merge_head(const MergeIn &in, int d, float *lds_red, float &M,
-                                           float &Z, Store store) {
+// s = grp, grp + NT/d, ... of output dim c online (one round trip of loads)
+// into LDS; after a barrier merge_final combines the groups.  lds_red: at
+// least 3*NT + 2 floats.
+template <int NT>
+__device__ __forceinline__ void merge_partials(const MergeIn &in, int d, float *lds_red) {
   const int tid = threadIdx.x;
   const int ng = NT / d, c = tid % d, grp = tid / d;
   float mx = -INFINITY, z = 0.0f, o = 0.0f;
@@ -50,26 +48,39 @@ __device__ __forceinline__ void merge_head(const MergeIn &in, int d, float *lds_
       mx = mn;
     }
   }
-  float *rm = lds_red, *rz = lds_red + NT, *ro = lds_red + 2 * NT;
-  rm[tid] = mx;
-  rz[tid] = z;
-  ro[tid] = o;
-  __syncthreads();
-  if (tid < d) {
-    float Mx = -INFINITY;
-    for (int g = 0; g < ng; ++g) Mx = fmaxf(Mx, rm[g * d + tid]);
-    float Zt = 0.0f, Ot = 0.0f;
-    for (int g = 0; g < ng; ++g) {
-      const float w = rm[g * d + tid] == -INFINITY ? 0.0f : __expf(rm[g * d + tid] - Mx);
-      Zt += rz[g * d + tid] * w;
-      Ot += ro[g * d + tid] * w;
-    }
-    store(tid, Ot / Zt);
-    if (tid == 0) {
-      lds_red[3 * NT] = Mx;
-      lds_red[3 * NT + 1] = Zt;
-    }
+  lds_red[tid] = mx;
+  lds_red[NT + tid] = z;
+  lds_red[2 * NT + tid] = o;
+}
+
+// Thread c of d: combines the groups of dim c, hands O_c / Z to `store(c, .)`;
+// M and Z go to lds_red[3 * NT] and [3 * NT + 1].
+template <int NT, typename Store>
+__device__ __forceinline__ void merge_final(int c, int d, float *lds_red, Store store) {
+  const int ng = NT / d;
+  const float *rm = lds_red, *rz = lds_red + NT, *ro = lds_red + 2 * NT;
+  float Mx = -INFINITY;
+  for (int g = 0; g < ng; ++g) Mx = fmaxf(Mx, rm[g * d + c]);
+  float Zt = 0.0f, Ot = 0.0f;
+  for (int g = 0; g < ng; ++g) {
+    const float w = rm[g * d + c] == -INFINITY ? 0.0f : __expf(rm[g * d + c] - Mx);
+    Zt += rz[g * d + c] * w;
+    Ot += ro[g * d + c] * w;
   }
+  store(c, Ot / Zt);
+  if (c == 0) {
+    lds_red[3 * NT] = Mx;
+    lds_red[3 * NT + 1] = Zt;
+  }
+}
+
+// Both steps; returns M and Z to every thread.
+template <int NT, typename Store>
+__device__ __forceinline__ void merge_head(const MergeIn &in, int d, float *lds_red, float &M,
+                                           float &Z, Store store) {
+  merge_partials<NT>(in, d, lds_red);
+  __syncthreads();
+  if ((int)threadIdx.x < d) merge_final<NT>(threadIdx.x, d, lds_red, store);
   __syncthreads();
   M = lds_red[3 * NT];
   Z = lds_red[3 * NT + 1];

@@ -148,44 +148,63 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return v;
 }
 
-// One wave: find the bin of hist[0..NB) (scanned from the top) holding the
-// rr-th element (1-based); returns the bin and the count strictly above it.
-// Each lane owns NB/64 consecutive bins (lane 0 the highest) in registers.
-template <int NB, int PT>
-__device__ __forceinline__ void find_digit(const uint32_t *hist, uint32_t rr, int &digit,
-                                           uint32_t &above) {
+// Max over the wave, in every lane (DPP inside 16-lane rows, swaps beyond).
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float x) {
+  return fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max_dpp(float x) {
+  x = dpp_max<0xB1>(x);   // lane ^ 1
+  x = dpp_max<0x4E>(x);   // lane ^ 2
+  x = dpp_max<0x141>(x);  // 8-lane mirror
+  x = dpp_max<0x140>(x);  // 16-lane mirror
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
+// One wave: find the bins of hist[0..NB) (scanned from the top) holding the
+// rr[x]-th elements (1-based) of NT targets: the bin, the count strictly above
+// it and its own count.  Each lane sums NB/64 consecutive bins (lane 0 the
+// highest) and a scan finds the target's lane; that lane's bins are then read
+// one per lane and scanned again.  (Walking them in the one lane instead took
+// 1700 cycles per target, 3400 of the 19600 of a 1237-token row; both
+// targets together now take about 1000.)
+template <int NB, int PT, int NT>
+__device__ __forceinline__ void find_digits(const uint32_t *hist, const uint32_t (&rr)[NT],
+                                            int (&digit)[NT], uint32_t (&above)[NT],
+                                            uint32_t (&count)[NT]) {
   constexpr int PER = NB / kWave;
   const int lane = threadIdx.x & 63;
   const int lo = NB - (lane + 1) * PER;  // this lane's bins: lo .. lo+PER-1
-  uint32_t hv[PER];
+  uint32_t s = 0;
 #pragma unroll
   for (int k = 0; k < PER; k += 4) {
     const uint4 v = *reinterpret_cast<const uint4 *>(hist + Hist<PT>::idx(lo) + k);  // inside one 32-bin group
-    hv[k] = v.x;
-    hv[k + 1] = v.y;
-    hv[k + 2] = v.z;
-    hv[k + 3] = v.w;
+    s += v.x + v.y + v.z + v.w;
   }
-  uint32_t s = 0;
-#pragma unroll
-  for (int k = 0; k < PER; ++k) s += hv[k];
   const uint32_t inc = wave_incl_scan(s);
   const uint32_t exc = inc - s;  // elements in the bins above this lane's
-  const uint64_t who = __ballot(exc < rr && rr <= inc);
-  const int src = who ? __ffsll((unsigned long long)who) - 1 : 0;
-  uint32_t cum = exc, ab = exc;
-  int dsel = lo;
-  bool found = false;
+  int top[NT];
+  uint32_t ab[NT], v[NT];
 #pragma unroll
-  for (int k = PER - 1; k >= 0; --k) {
-    const bool hit = !found && cum + hv[k] >= rr;
-    dsel = hit ? lo + k : dsel;
-    ab = hit ? cum : ab;
-    found = found || hit;
-    cum += hv[k];
+  for (int x = 0; x < NT; ++x) {
+    const uint64_t who = ballot(exc < rr[x] && rr[x] <= inc);
+    const int src = who ? __builtin_ctzll(who) : 0;
+    top[x] = NB - 1 - src * PER;  // its highest bin
+    ab[x] = __builtin_amdgcn_readlane(exc, src);
+    v[x] = lane < PER ? hist[Hist<PT>::idx(max(top[x] - lane, 0))] : 0u;
   }
-  digit = __shfl(dsel, src, kWave);
-  above = __shfl(ab, src, kWave);
+#pragma unroll
+  for (int x = 0; x < NT; ++x) {
+    const uint32_t in2 = wave_incl_scan(v[x]);
+    const uint64_t hit = ballot(lane < PER && ab[x] + in2 >= rr[x]);
+    const int at = hit ? __builtin_ctzll(hit) : PER - 1;
+    digit[x] = top[x] - at;
+    count[x] = __builtin_amdgcn_readlane(v[x], at);
+    above[x] = ab[x] + __builtin_amdgcn_readlane(in2, at) - count[x];
+  }
 }
 
 template <int PT, int CAP>
@@ -236,8 +255,12 @@ __device__ __forceinline__ void row_setup(const PartArgs &a, RowCtx &r) {
   }
 }
 
-// Row max and sum: combined from stage 1's chunk records (fused; also writes
-// the head's output) or read back.
+// The row's max and sum: read back, or (fused) combined from stage 1's chunk
+// records.  The passes need only the max at first, which every wave takes
+// from the records by itself; the records' combination (which also gives the
+// head's output) runs beside the select: its groups go to LDS here, and
+// finish_merge, by the workgroup's last d threads after the next barrier,
+// combines them.
 template <bool kMerge, int PT, int CAP>
 __device__ __forceinline__ void row_stats(const PartArgs &a, PartShared<PT, CAP> &sh, RowCtx &r) {
   if constexpr (kMerge) {
@@ -247,22 +270,34 @@ __device__ __forceinline__ void row_stats(const PartArgs &a, PartShared<PT, CAP>
     in.stride = (int64_t)a.gp * (a.d + 2);
     in.part = a.part + (int64_t)unit * a.n_split * in.stride + i * (a.d + 2);
     in.nv = (r.n + a.chunk - 1) / a.chunk;
-    void *out = a.small_out;
-    const int64_t o0 = (int64_t)r.row * a.d;
-    const bool bf = a.out_bf16;
-    merge_head<PT>(in, a.d, sh.mred, r.M, r.Z, [&](int c, float v) {
-      if (bf)
-        elem<bf16_t>::store1(out, o0 + c, v);
-      else
-        elem<float>::store1(out, o0 + c, v);
-    });
-    if (threadIdx.x == 0) {
-      a.row_max[r.row] = r.M;
-      a.row_sum[r.row] = r.Z;
-    }
+    float mx = -INFINITY;
+    for (int s = threadIdx.x & 63; s < in.nv; s += kWave) mx = fmaxf(mx, in.part[s * in.stride]);
+    merge_partials<PT>(in, a.d, sh.mred);
+    r.M = wave_max_dpp(mx);
   } else {
     r.M = a.row_max[r.row];
     r.Z = a.row_sum[r.row];
+  }
+}
+
+template <bool kMerge, int PT, int CAP>
+__device__ __forceinline__ void finish_merge(const PartArgs &a, PartShared<PT, CAP> &sh, const RowCtx &r) {
+  if constexpr (kMerge) {
+    const int c = (int)threadIdx.x - (PT - a.d);
+    if (c < 0) return;
+    void *out = a.small_out;
+    const int64_t o0 = (int64_t)r.row * a.d;
+    const bool bf = a.out_bf16;
+    merge_final<PT>(c, a.d, sh.mred, [&](int k, float v) {
+      if (bf)
+        elem<bf16_t>::store1(out, o0 + k, v);
+      else
+        elem<float>::store1(out, o0 + k, v);
+    });
+    if (c == 0) {
+      a.row_max[r.row] = sh.mred[3 * PT];
+      a.row_sum[r.row] = sh.mred[3 * PT + 1];
+    }
   }
 }
 
@@ -382,14 +417,22 @@ struct Targets {
   uint32_t eq[2];    // tokens equal to T in the row
 };
 
-// Steps 1 and 2.
-template <int PT, int CAP, typename Row>
-__device__ __forceinline__ Targets select_targets(PartShared<PT, CAP> &sh, const RowCtx &r, const Row &row) {
+// Steps 1 and 2 (with the end of the merge: finish_merge).
+template <bool kMerge, int PT, int CAP, typename Row>
+__device__ __forceinline__ Targets select_targets(const PartArgs &a, PartShared<PT, CAP> &sh, const RowCtx &r,
+                                                  const Row &row) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // The targets' ranks count ranked (older) tokens only.  Rank 0 -- no
   // ranked token in the set -- is resolved as rank 1 and then replaced by a
   // key above every logit's.
-  if (r.ntop + r.nm == 0) return Targets{{~0u, ~0u}, {0u, 0u}, {0u, 0u}};
+  if (r.ntop + r.nm == 0) {
+    if constexpr (kMerge) {
+      __syncthreads();
+      finish_merge<kMerge>(a, sh, r);
+      __syncthreads();
+    }
+    return Targets{{~0u, ~0u}, {0u, 0u}, {0u, 0u}};
+  }
   for (int x = tid; x < Hist<PT>::size; x += PT) sh.hist[0][x] = 0;
   if (tid < 2) sh.ncand[tid] = 0;
   __syncthreads();
@@ -400,14 +443,10 @@ __device__ __forceinline__ Targets select_targets(PartShared<PT, CAP> &sh, const
   // every wave finds both targets' bins itself: no broadcast needed
   uint32_t rr[2] = {(uint32_t)max(r.ntop, 1), (uint32_t)(r.ntop + r.nm)};
   int bin[2];
-  uint32_t cnt[2];
+  uint32_t cnt[2], above[2];
+  find_digits<kBins, PT, 2>(sh.hist[0], rr, bin, above, cnt);
 #pragma unroll
-  for (int x = 0; x < 2; ++x) {
-    uint32_t above;
-    find_digit<kBins, PT>(sh.hist[0], rr[x], bin[x], above);
-    rr[x] -= above;
-    cnt[x] = sh.hist[0][Hist<PT>::idx(bin[x])];
-  }
+  for (int x = 0; x < 2; ++x) rr[x] -= above[x];
   // 0: rank by counting, 1: radix over LDS candidates, 2: radix over the row
   int mode[2];
 #pragma unroll
@@ -444,6 +483,7 @@ __device__ __forceinline__ Targets select_targets(PartShared<PT, CAP> &sh, const
     sh.sel[tid][2] = rr[tid];
   }
   __syncthreads();  // candidates visible
+  finish_merge<kMerge>(a, sh, r);  // (the last waves; the first ones count)
   // Counting: key k of target x's bin against all n of the bin's keys.
   auto count = [&](int x, uint32_t k, uint32_t n, uint32_t rank) {
     const uint32_t key = sh.cand[x][k];
@@ -503,17 +543,18 @@ __device__ __forceinline__ Targets select_targets(PartShared<PT, CAP> &sh, const
         });
       __syncthreads();
       if (wave < 2 && mode[wave] != 0) {
-        int digit;
-        uint32_t above;
+        int digit[1];
+        uint32_t above[1], count[1];
+        const uint32_t rank[1] = {sh.sel[wave][2]};
         if (pass < 2)
-          find_digit<2048, PT>(sh.hist[wave], sh.sel[wave][2], digit, above);
+          find_digits<2048, PT, 1>(sh.hist[wave], rank, digit, above, count);
         else
-          find_digit<1024, PT>(sh.hist[wave], sh.sel[wave][2], digit, above);
+          find_digits<1024, PT, 1>(sh.hist[wave], rank, digit, above, count);
         if (lane == 0) {
-          sh.sel[wave][0] |= (uint32_t)digit << shf;
+          sh.sel[wave][0] |= (uint32_t)digit[0] << shf;
           sh.sel[wave][1] |= dmask << shf;
-          sh.sel[wave][2] -= above;
-          sh.sel[wave][3] = sh.hist[wave][Hist<PT>::idx(digit)];  // after the last pass: count of T
+          sh.sel[wave][2] -= above[0];
+          sh.sel[wave][3] = count[0];  // after the last pass: count of T
         }
       }
     }
@@ -781,7 +822,9 @@ void partition_kernel(PartArgs a) {
   row.load();  // in flight while the row's statistics arrive
   row_stats<kMerge>(a, sh, r);
   row.set_max(r.M);
-  Compactor cp(r, select_targets(sh, r, row), 1.0f / r.Z);
+  const Targets tg = select_targets<kMerge>(a, sh, r, row);
+  if constexpr (kMerge) r.Z = sh.mred[3 * PT + 1];
+  Compactor cp(r, tg, 1.0f / r.Z);
   // ties at a threshold split between two sets need their ranks in token order
   const bool split = cp.t.need[0] < cp.t.eq[0] || cp.t.need[1] < cp.t.eq[1];
   const bool offs = kMerge && a.tab;
