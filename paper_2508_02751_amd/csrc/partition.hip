@@ -28,7 +28,7 @@
 // registers (one exchange); longer rows are re-read per pass, 16 slots in
 // flight, the candidate gather from the row's end (it starts on what the
 // histogram pass read last).  Many rows (several per CU) get 256 threads
-// each, so that more rows are resident (six re-read rows per CU); few rows
+// each, so that more rows are resident (six per CU); few rows
 // get 512, or 1024 when there is at most one per CU.  The fused variant
 // first combines stage 1's per-chunk records of its head (row max, row sum,
 // the head's output), so a step needs no separate merge launch.
@@ -59,15 +59,16 @@ template <int PT>
 struct PC {
   static constexpr int waves = PT / kWave;
 };
-// Rows resident per CU: six for the long 256-thread rows (the many-row
-// launches, where more rows in flight hide the passes' latency: 80 VGPRs),
-// four otherwise (the register rows need up to 128 VGPRs).
+// Rows resident per CU: six of 256 threads (the many-row launches, where more
+// rows in flight hide the passes' latency: 80 VGPRs), four otherwise.
 template <int R, int PT>
-constexpr int rows_per_cu() { return R == 0 && PT == 256 ? 6 : 4; }
-// Candidate keys per target kept in LDS: 512 in the long 256-thread rows,
-// so that six of them fit a CU's LDS, else 2048.
+constexpr int rows_per_cu() { return PT == 256 ? 6 : 4; }
+// Candidate keys per target kept in LDS: 512 in the 256-thread rows, so that
+// six of them fit a CU's LDS, else 2048.  (Ragged batch of 64 sequences of up
+// to 4096 tokens, 21504 rows: four rows per CU with 2048 keys 274 us, five with 1024
+// 245, six with 512 226.)
 template <int R, int PT>
-constexpr int cand_cap() { return R == 0 && PT == 256 ? 512 : 2048; }
+constexpr int cand_cap() { return PT == 256 ? 512 : 2048; }
 // Slots of a long row per workgroup exchange (and in flight while a group is
 // compacted)
 constexpr int kGroup = 16;
