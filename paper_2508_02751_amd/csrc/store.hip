@@ -63,16 +63,53 @@ __device__ __forceinline__ int block_exscan(int v, int *red, int &total) {
   return base + x - v;
 }
 
-// The source code of token t's row in a union: its row in the old store
-// when the old slot map holds it, else its row of the full store.
-__device__ __forceinline__ int32_t row_source(const int32_t *old_slot, int64_t sbase, int t,
-                                              int64_t rows) {
-  const int os = old_slot ? old_slot[sbase + t] : -1;
+// The source code of token t's row in a union: its row `os` in the old store
+// when the old slot map holds the token, else its row of the full store.
+__device__ __forceinline__ int32_t row_source(int os, int t, int64_t rows) {
   return (os >= 0 && os < rows) ? os : -(t + 1);
+}
+
+constexpr int kHeads = 8;
+
+// Sets the members of the lists of HB heads at `rows` (heads of them, the rest
+// skipped): IB entries of every head per thread and pass, all loads of a pass
+// in flight before any is used.  (A flat walk over all heads' entries, which
+// found each entry's head by a division and its row through the head map, and
+// old slots read one token at a time below, took 22 us for the index of a
+// Qwen2-7B step.)
+template <int HB, int IB>
+__device__ __forceinline__ void mark(const StoreArgs &a, const int64_t *rows, int heads, int n,
+                                     uint32_t *bk, uint32_t *bv) {
+  const int per = a.kc_cap + a.km_cap;
+  for (int i0 = threadIdx.x; i0 < per; i0 += IB * kIT) {
+    int tok[IB][HB];
+#pragma unroll
+    for (int q = 0; q < IB; ++q) {
+      const int i = i0 + q * kIT;
+#pragma unroll
+      for (int h = 0; h < HB; ++h) {
+        tok[q][h] = -1;
+        if (h < heads && i < per)
+          tok[q][h] = i < a.kc_cap ? a.crit[rows[h] * a.kc_cap + i]
+                                   : a.marg[rows[h] * a.km_cap + (i - a.kc_cap)];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < IB; ++q)
+#pragma unroll
+      for (int h = 0; h < HB; ++h) {
+        const int t = tok[q][h];
+        if (t >= 0 && t < n) {
+          if (i0 + q * kIT < a.kc_cap) atomicOr(&bk[t >> 5], 1u << (t & 31));
+          atomicOr(&bv[t >> 5], 1u << (t & 31));
+        }
+      }
+  }
 }
 
 __global__ __launch_bounds__(kIT) void store_index(StoreArgs a) {
   extern __shared__ uint32_t smem[];  // bits K [words], bits V [words], word ranks K, V
+  __shared__ int64_t rows[kHeads];    // the lists' rows of up to kHeads query heads
   uint32_t *bk = smem, *bv = smem + a.words;
   int *rk = reinterpret_cast<int *>(smem + 2 * a.words), *rv = rk + a.words;
   __shared__ int red[kIT / kWave];
@@ -81,43 +118,22 @@ __global__ __launch_bounds__(kIT) void store_index(StoreArgs a) {
   const int n = clampi(a.seq_len[b], 1, a.n_cap);
   const int nw = (n + 31) / 32;
   for (int w = threadIdx.x; w < nw; w += kIT) bk[w] = bv[w] = 0u;
-  __syncthreads();
+  if (a.select) __syncthreads();  // (else the rows' barrier below)
   // membership from the lists of the group's query heads (one shared set
   // per kv head with group selection); -1 padding and anything outside
-  // [0, n) ignored.  Entry e of the flat walk: head e / per, then its
-  // critical list, then its marginal list.
-  const int heads = a.select ? 1 : a.g;
-  const int per = a.kc_cap + a.km_cap;
-  const int total = heads * per;
-  constexpr int kBatch = 8;
-  for (int e0 = threadIdx.x; e0 < total; e0 += kBatch * kIT) {
-    int tok[kBatch];
-    bool crit[kBatch];
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) {  // every load issued before any use
-      const int e = e0 + k * kIT;
-      tok[k] = -1;
-      crit[k] = false;
-      if (e < total) {
-        const int h = e / per, i = e - h * per;
-        int64_t row;
-        if (a.select) {
-          row = unit;
-        } else {
-          const int j = clampi(a.head_map[layer * a.hq + kvh * a.g + h], 0, a.nsh - 1);
-          row = (int64_t)b * a.nsh + j;
-        }
-        crit[k] = i < a.kc_cap;
-        tok[k] = crit[k] ? a.crit[row * a.kc_cap + i] : a.marg[row * a.km_cap + (i - a.kc_cap)];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const int t = tok[k];
-      if (t >= 0 && t < n) {
-        if (crit[k]) atomicOr(&bk[t >> 5], 1u << (t & 31));
-        atomicOr(&bv[t >> 5], 1u << (t & 31));
-      }
+  // [0, n) ignored
+  if (a.select) {
+    const int64_t row = unit;
+    mark<1, 8>(a, &row, 1, n, bk, bv);
+  } else {
+    for (int h0 = 0; h0 < a.g; h0 += kHeads) {
+      const int heads = min(kHeads, a.g - h0);
+      if (h0 > 0) __syncthreads();  // the rows before are read
+      if ((int)threadIdx.x < heads)
+        rows[threadIdx.x] = (int64_t)b * a.nsh +
+                            clampi(a.head_map[layer * a.hq + kvh * a.g + h0 + (int)threadIdx.x], 0, a.nsh - 1);
+      __syncthreads();
+      mark<kHeads, 2>(a, rows, heads, n, bk, bv);
     }
   }
   __syncthreads();
@@ -140,26 +156,42 @@ __global__ __launch_bounds__(kIT) void store_index(StoreArgs a) {
   __syncthreads();
   // slot maps and the rows' sources
   const int64_t sbase = (int64_t)unit * a.n_cap, ubase = (int64_t)unit * a.rows;
-  for (int t = threadIdx.x; t < n; t += kIT) {
-    const uint32_t below = (1u << (t & 31)) - 1u;
-    const uint32_t wk = bk[t >> 5], wv = bv[t >> 5];
-    int sk = -1, sv = -1;
-    if (wk >> (t & 31) & 1u) {
-      const int r = rk[t >> 5] + __popc(wk & below);
-      if (r < a.rows) {
-        sk = r;
-        a.src_k[ubase + r] = row_source(a.old_k ? a.old_k_slot : nullptr, sbase, t, a.rows);
+  constexpr int kTok = 4;  // tokens per thread and pass, their old slots in flight together
+  for (int tb = threadIdx.x; tb < n; tb += kTok * kIT) {
+    int ock[kTok], ocv[kTok];
+#pragma unroll
+    for (int q = 0; q < kTok; ++q) {
+      const int t = tb + q * kIT;
+      ock[q] = ocv[q] = -1;
+      if (a.old_k && t < n) {
+        ock[q] = a.old_k_slot[sbase + t];
+        ocv[q] = a.old_v_slot[sbase + t];
       }
     }
-    if (wv >> (t & 31) & 1u) {
-      const int r = rv[t >> 5] + __popc(wv & below);
-      if (r < a.rows) {
-        sv = r;
-        a.src_v[ubase + r] = row_source(a.old_v ? a.old_v_slot : nullptr, sbase, t, a.rows);
+#pragma unroll
+    for (int q = 0; q < kTok; ++q) {
+      const int t = tb + q * kIT;
+      if (t >= n) break;
+      const uint32_t below = (1u << (t & 31)) - 1u;
+      const uint32_t wk = bk[t >> 5], wv = bv[t >> 5];
+      int sk = -1, sv = -1;
+      if (wk >> (t & 31) & 1u) {
+        const int r = rk[t >> 5] + __popc(wk & below);
+        if (r < a.rows) {
+          sk = r;
+          a.src_k[ubase + r] = row_source(ock[q], t, a.rows);
+        }
       }
+      if (wv >> (t & 31) & 1u) {
+        const int r = rv[t >> 5] + __popc(wv & below);
+        if (r < a.rows) {
+          sv = r;
+          a.src_v[ubase + r] = row_source(ocv[q], t, a.rows);
+        }
+      }
+      a.k_slot[sbase + t] = sk;
+      a.v_slot[sbase + t] = sv;
     }
-    a.k_slot[sbase + t] = sk;
-    a.v_slot[sbase + t] = sv;
   }
   if (threadIdx.x == 0) {
     a.counts[2 * (int64_t)unit] = tk;
