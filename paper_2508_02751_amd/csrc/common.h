@@ -115,6 +115,54 @@ __device__ __forceinline__ float cw_exp(float x) {
   return ldexpf(p, (int)k);
 }
 
+// Probabilities from exponentials scaled by 2^64 (exact: e is 0 or 2^-116 ..
+// 1), so that no remainder of the divisions below is subnormal.
+constexpr float kUp = 0x1p64f, kDown = 0x1p-64f;
+
+// cw_exp(x) * 2^64, without a branch: x / ln 2 is rounded to an integer by
+// adding 1.5 * 2^23 (+ 64: even, so ties still go to even), whose low bits
+// then are the exponent to add to the polynomial's (0.7 .. 1.42).
+__device__ __forceinline__ float exp_up(float x) {
+#pragma clang fp contract(off)
+  constexpr float kMagic = 0x1.8p23f + 64.0f;
+  const float t = __fadd_rn(__fmul_rn(x, 0x1.715476p+0f), kMagic);
+  const float k = __fsub_rn(t, kMagic);
+  float r = __builtin_fmaf(-k, 0x1.62e4p-1f, x);
+  r = __builtin_fmaf(-k, 0x1.7f7d1cp-20f, r);
+  float p = 0x1.a01a02p-13f;
+  p = __builtin_fmaf(p, r, 0x1.6c16c2p-10f);
+  p = __builtin_fmaf(p, r, 0x1.111112p-7f);
+  p = __builtin_fmaf(p, r, 0x1.555556p-5f);
+  p = __builtin_fmaf(p, r, 0x1.555556p-3f);
+  p = __builtin_fmaf(p, r, 0.5f);
+  p = __builtin_fmaf(p, r, 1.0f);
+  p = __builtin_fmaf(p, r, 1.0f);
+  const float e = __uint_as_float(__float_as_uint(p) + (__float_as_uint(t) << 23));
+  return x >= -80.0f ? e : 0.0f;
+}
+
+// e / Z correctly rounded, from 1 / Z in two parts (y its rounded value, dy the
+// rest): the quotient by both is within an ulp, and from there one correction
+// by its exact remainder rounds correctly (Markstein's theorem).  4
+// instructions against the 13 of a general division.  Z = 0 (y infinite, dy
+// NaN) gives NaN, as 0 / 0 does.
+struct Recip {
+  float z, y, dy;
+};
+__device__ __forceinline__ Recip recip(float z) {
+#pragma clang fp contract(off)
+  Recip r;
+  r.z = z;
+  r.y = __fdiv_rn(1.0f, z);
+  r.dy = __fmul_rn(__builtin_fmaf(-r.y, z, 1.0f), r.y);
+  return r;
+}
+__device__ __forceinline__ float div_by(float e, const Recip &r) {
+#pragma clang fp contract(off)
+  const float q = __builtin_fmaf(e, r.y, __fmul_rn(e, r.dy));
+  return __builtin_fmaf(__builtin_fmaf(-q, r.z, e), r.y, q);
+}
+
 // Order-preserving uint32 key of an fp32 logit; -0 and +0 share a key.
 __device__ __forceinline__ uint32_t logit_key(float s) {
   uint32_t u = __float_as_uint(s == 0.0f ? 0.0f : s);

@@ -56,6 +56,17 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
   return v;
 }
 
+// e / Z of e = es * 2^-64 (es from exp_up), correctly rounded: 5 instructions
+// with the row's reciprocal where the quotient is surely normal (Z is between
+// 1 and the row's length), else the general division.
+__device__ __forceinline__ float prob_of(float es, const Recip &r) {
+  const float p = div_by(es, r) * kDown;
+  // es in (0, 2^-30): e < 2^-94, rare
+  const bool tiny = __float_as_uint(es) - 1u < 0x30800000u - 1u;
+  if (__builtin_expect(__any(tiny), 0)) return tiny ? __fdiv_rn(es * kDown, r.z) : p;
+  return p;
+}
+
 constexpr int kZqTok = 8 * kGT;     // tokens per group_zq workgroup (8 per thread)
 constexpr int kScoreTok = 4 * kGT;  // tokens per group_scores workgroup (4 per thread)
 
@@ -78,8 +89,8 @@ __global__ __launch_bounds__(kGT) void group_zq(GroupSelArgs a) {
   for (int q = 0; q < kZqTok / kGT; ++q) {
     const int t = t0 + q * kGT + threadIdx.x;
     if (t < n) {
-      const float e = cw_exp(__fsub_rn(lg[t], m));
-      z += (uint64_t)__float2ull_rz(__fmul_rn(e, 0x1p40f));  // exact scaling, truncation
+      const float e = exp_up(__fsub_rn(lg[t], m));
+      z += (uint64_t)__float2ull_rz(__fmul_rn(e, 0x1p-24f));  // e * 2^40: exact scaling, truncation
     }
   }
   z = wave_sum_u64(z);
@@ -107,7 +118,8 @@ __global__ __launch_bounds__(kGT) void group_scores(GroupSelArgs a) {
   constexpr int kMaxGQ = 16;
   constexpr int kQ = kScoreTok / kGT;
   __shared__ const float *lrow[kMaxGQ];
-  __shared__ float lm[kMaxGQ], lz[kMaxGQ], wmax[kGT / kWave];
+  __shared__ float lm[kMaxGQ], wmax[kGT / kWave];
+  __shared__ Recip lz[kMaxGQ];
   const int grow = blockIdx.x;
   const int per = a.L * a.hkv, b = grow / per, layer = (grow % per) / a.hkv, kvh = grow % a.hkv;
   const int n = clampi(a.seq_len[b], 1, a.n_cap);
@@ -119,7 +131,7 @@ __global__ __launch_bounds__(kGT) void group_scores(GroupSelArgs a) {
     const int64_t row = (int64_t)b * a.nsh + j;
     lrow[h] = a.logits + row * a.n_cap;
     lm[h] = a.row_max[row];
-    lz[h] = zq_of(a, row);
+    lz[h] = recip(zq_of(a, row));
   }
   __syncthreads();
   float f[kQ];
@@ -127,12 +139,16 @@ __global__ __launch_bounds__(kGT) void group_scores(GroupSelArgs a) {
   for (int q = 0; q < kQ; ++q) f[q] = 0.0f;
   for (int h = 0; h < a.gq; ++h) {
     const float *lg = lrow[h];
-    const float m = lm[h], z = lz[h];
+    const float m = lm[h];
+    const Recip z = lz[h];
+    float x[kQ];
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) {  // kQ independent chains; heads in ascending order
-      const int t = t0 + q * kGT + threadIdx.x;
-      if (t < n) f[q] = __fadd_rn(f[q], __fdiv_rn(cw_exp(__fsub_rn(lg[t], m)), z));
+    for (int q = 0; q < kQ; ++q) {  // (tokens past n repeat the last one and are not kept)
+      x[q] = lg[min(t0 + q * kGT + (int)threadIdx.x, n - 1)];
     }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q)  // kQ independent chains; heads in ascending order
+      f[q] = __fadd_rn(f[q], prob_of(exp_up(__fsub_rn(x[q], m)), z));
   }
   float *out = a.keys + (int64_t)grow * a.n_cap;
   float fmx = 0.0f;
@@ -165,7 +181,7 @@ __global__ __launch_bounds__(kGT) void accum_scores(GroupSelArgs a) {
   const int t0 = blockIdx.y * kScoreTok;
   if (t0 >= n) return;
   const float m = a.row_max[row];
-  const float z = zq_of(a, row);
+  const Recip z = recip(zq_of(a, row));
   const float *lg = a.logits + (int64_t)row * a.n_cap;
   float *acc = a.acc + (int64_t)row * a.n_cap;
   float fmx = 0.0f;
@@ -173,7 +189,7 @@ __global__ __launch_bounds__(kGT) void accum_scores(GroupSelArgs a) {
   for (int q = 0; q < kQ; ++q) {
     const int t = t0 + q * kGT + threadIdx.x;
     if (t < n) {
-      const float f = __fadd_rn(acc[t], __fdiv_rn(cw_exp(__fsub_rn(lg[t], m)), z));
+      const float f = __fadd_rn(acc[t], prob_of(exp_up(__fsub_rn(lg[t], m)), z));
       acc[t] = f;
       fmx = fmaxf(fmx, f);
     }
@@ -212,9 +228,9 @@ __global__ __launch_bounds__(kGT) void group_weights(GroupSelArgs a) {
   const float *lg = a.logits + row * a.n_cap;
   const int32_t *crit = a.crit + grow * a.kc_cap, *marg = a.marg + grow * a.km_cap;
   const int last = sz.n - 1;
-  // four entries per thread per pass: their list loads, then their logit
+  // eight entries per thread per pass: their list loads, then their logit
   // loads, are in flight together (each thread still adds in k order)
-  constexpr int kB = 4;
+  constexpr int kB = 8;
   float sc = 0.0f, sm = 0.0f;
   for (int k0 = threadIdx.x; k0 < sz.nc; k0 += kB * kGT) {
     int t[kB];
