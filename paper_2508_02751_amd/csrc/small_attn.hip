@@ -487,6 +487,15 @@ __global__ __launch_bounds__(kThreads) void small_attn_valu(SmallArgs a) {
   for (int tb = u.t0; tb < u.t1; tb += TILE) {
     const int nr = min(TILE, u.t1 - tb);
     stage_k<float, D>(tile, kb + (int64_t)tb * C::ROWB, nr);
+    // the tile's V rows travel while its K rows are used
+    constexpr int NV = TILE * C::V16 / kThreads;
+    uint4 vpre[NV];
+#pragma unroll
+    for (int r = 0; r < NV; ++r) {
+      const int x = tid + r * kThreads, row = x / C::V16;
+      vpre[r] = row < nr ? stream16(vb + (int64_t)(tb + row) * C::ROWB + x % C::V16 * 16)
+                         : make_uint4(0u, 0u, 0u, 0u);
+    }
     __syncthreads();
     float s[GP];
 #pragma unroll
@@ -504,10 +513,13 @@ __global__ __launch_bounds__(kThreads) void small_attn_valu(SmallArgs a) {
           lrow[(int64_t)i * a.n_cap + tb + tid] = s[i];
         }
     }
+    {
+      float t[GP];
 #pragma unroll
-    for (int i = 0; i < GP; ++i) {
-      const float v = wave_max(s[i]);
-      if (lane == 0) red[wave * GP + i] = v;
+      for (int i = 0; i < GP; ++i) t[i] = s[i];
+      const float mx = wave_reduce_heads<GP, true>(t);
+      constexpr int sh = head_shift<GP>();
+      if ((lane & ((1 << sh) - 1)) == 0) red[wave * GP + (lane >> sh)] = mx;
     }
     __syncthreads();
     float alpha[GP];
@@ -524,7 +536,11 @@ __global__ __launch_bounds__(kThreads) void small_attn_valu(SmallArgs a) {
       for (int c = 0; c < VD; ++c) acc[i][c] *= alpha[i];
     }
     // V tile replaces the K tile
-    stage_k<float, D>(tile, vb + (int64_t)tb * C::ROWB, nr);
+#pragma unroll
+    for (int r = 0; r < NV; ++r) {
+      const int x = tid + r * kThreads;
+      *reinterpret_cast<uint4 *>(tile + x / C::V16 * C::ROWS + x % C::V16 * 16) = vpre[r];
+    }
     __syncthreads();
     for (int t = tp; t < nr; t += NTP) {
       float vv[VD];
@@ -539,17 +555,25 @@ __global__ __launch_bounds__(kThreads) void small_attn_valu(SmallArgs a) {
     }
     __syncthreads();
   }
-#pragma unroll
-  for (int i = 0; i < GP; ++i) {
-    const float v = wave_sum(z_thr[i]);
-    if (lane == 0) red[wave * GP + i] = v;
+  {
+    const float zs = wave_reduce_heads<GP, false>(z_thr);
+    constexpr int sh = head_shift<GP>();
+    if ((lane & ((1 << sh) - 1)) == 0) red[wave * GP + (lane >> sh)] = zs;
   }
+  // sum over the lanes that hold one dim group: 16 (d 64) and 32 lanes apart
+  static_assert(NDG == 16 || NDG == 32, "dim groups per wave");
 #pragma unroll
-  for (int o = NDG; o < kWave; o <<= 1)
+  for (int i = 0; i < GP; ++i)
 #pragma unroll
-    for (int i = 0; i < GP; ++i)
-#pragma unroll
-      for (int c = 0; c < VD; ++c) acc[i][c] += __shfl_xor(acc[i][c], o, kWave);
+    for (int c = 0; c < VD; ++c) {
+      uint32_t x = __float_as_uint(acc[i][c]);
+      if (NDG == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        x = __float_as_uint(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+      }
+      const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+      acc[i][c] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
   float *buf = reinterpret_cast<float *>(tile);  // [4 waves][GP][D]
   static_assert(4 * GP * D * 4 <= TILE * C::ROWS, "reduction buffer fits the tile");
   if (lane < NDG) {
