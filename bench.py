@@ -51,7 +51,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, 8 TB/s
-FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X fp32 vector (packed FMA counted as 4 flops)
+FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X fp32, vector (packed FMA counted as 4 flops) and matrix
 DEFAULT_STEPS = {2: 100, 4: 256}  # others: 20
 FLUSH_BYTES = 1 << 30  # written before each flushed step: above L2 and the 256 MB MALL
 
@@ -870,7 +870,7 @@ def bench_match(args):
             "top_k": int(x["top_k"][0]), "launch": "eager" if args.eager else "hip-graph",
         },
         "roofline": {
-            "kernel": "match_logits+match_rowsum+match_scores+match_map",
+            "kernel": "match_heads+match_map",
             "bound": "alu",
             "achieved": achieved,
             "peak": FP32_VECTOR_PEAK_TFLOPS,

@@ -39,9 +39,7 @@ KERNEL_SOURCES = {
     "hybrid_kernel": "hybrid.hip",
     "hybrid_group_kernel": "hybrid_group.hip",
     "hybrid_group_merge": "hybrid_group.hip",
-    "match_logits": "match.hip",
-    "match_rowsum": "match.hip",
-    "match_scores": "match.hip",
+    "match_heads": "match.hip",
     "match_map": "match.hip",
     "group_zq": "group_select.hip",
     "group_scores": "group_select.hip",

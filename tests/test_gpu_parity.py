@@ -108,12 +108,20 @@ def flat_small_keys(x):
 
 @pytest.mark.parametrize("n", [800, 3000, 6000])
 def test_constant_logits_many_rows(n):
-    """The same ties over 1024 rows, so 256 threads per row: register rows
-    keep up to 2048 candidate keys in LDS (the whole-row bin is ranked there
-    at 800 tokens, over the row at 3000), rows re-read per pass (six per CU)
-    up to 512 (over the row at 6000)."""
+    """The same ties over 1024 rows, so 256 threads per row, which keep up to
+    512 candidate keys in LDS: the whole-row bin is ranked over the row, in
+    registers (800 and 3000 tokens) or re-read per pass (6000)."""
     small = W.ModelShape(4, 16, 4, 64)
     w = custom(f"const-many-{n}", 117, 16, n, "bf16", small, LARGE, ("pct", 10), ("pct", 25))
+    run_case(w, mutate=flat_small_keys)
+
+
+@pytest.mark.parametrize("n", [256, 257, 512, 513])
+def test_constant_logits_at_the_candidate_limits(n):
+    """Register rows of 256 threads whose one bin is just countable (256 keys),
+    just ranked in LDS (257, 512) and just too large for it (513)."""
+    small = W.ModelShape(4, 16, 4, 64)
+    w = custom(f"const-limit-{n}", 119, 16, n, "bf16", small, LARGE, ("pct", 10), ("pct", 25))
     run_case(w, mutate=flat_small_keys)
 
 
@@ -464,6 +472,21 @@ def test_group_selection_ragged_with_recent_tokens():
                W.ModelShape(2, 14, 2, 128), ("pct", 8), ("pct", 15), ragged_min=50,
                recent=("pct", 4))
     run_case(w, mutate=group_sel)
+
+
+def test_group_selection_of_tiny_probabilities():
+    """Queries 4x scaled: about half of a row's exponentials are below 2^-94,
+    where quotients could be subnormal, and a third are zero; the budgets take
+    in both ranges."""
+    w = custom("gsel-tiny", 124, 2, 1100, "bf16", SMALL, LARGE, ("pct", 40), ("pct", 40))
+
+    def spread(x):
+        group_sel(x)
+        x["s_q"] = (4.0 * x["s_q"].float()).to(x["s_q"].dtype)
+
+    ps, _, _ = run_case(w, mutate=spread)
+    low = ps.buf.logits - ps.buf.row_max[..., None]
+    assert (low < -80).any() and ((low > -80) & (low < -66)).any()
 
 
 def test_group_selection_repeats_bit_identically():

@@ -98,6 +98,24 @@ def test_store_from_a_step(select, dtype):
     check_store(sc, oracle_store(x, ps, rows, select), x, f"store select={select} {dtype}")
 
 
+@pytest.mark.parametrize("g", [1, 8, 9, 16])
+def test_store_group_sizes(g):
+    """Lists are marked eight heads at a time: one pass full, part of one, two."""
+    S, W, prepare_step = modules()
+    w = W.Workload(136, f"store-g{g}", 2, 1300, "bf16", W.ModelShape(2, 8, 2, 64),
+                   W.ModelShape(2, 2 * g, 2, 128), ("pct", 8), ("pct", 15), ragged_min=500)
+    x = W.make_step_inputs(w, DEV)
+    ps = prepare_step(x)
+    ps.run()
+    rows = capacity(x, g)
+    sc = S.prepare_store(ps.batch, ps.head_map, ps.buf.logits.shape[1], ps.buf.crit_idx,
+                         ps.buf.marg_idx, x["l_k"], x["l_v"], rows)
+    log(f"[store] groups of {g}: {rows} rows per kv head")
+    sc.run()
+    torch.cuda.synchronize()
+    check_store(sc, oracle_store(x, ps, rows, 0), x, f"store, groups of {g}")
+
+
 def test_store_reuses_the_previous_store_across_steps():
     """Two drifting steps; the previous store (the library's and, separately,
     the oracle's) is altered so that the source of every row (old store or
