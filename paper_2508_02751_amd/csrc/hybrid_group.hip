@@ -85,6 +85,10 @@ struct GroupArgs {
   int group_sel;    // lists per (b, layer, kv head), marg_prob/mass per query head
 };
 
+// The membership words read or written by halves (they are set and cleared as
+// 32-bit words: accesses of both types meet in one object)
+typedef uint16_t __attribute__((may_alias)) half_word_t;
+
 struct WaveTiles {
   unsigned char vt[kVTBytes];   // V^T of the block (dims x rows), later the wave's O
   float p[16][kPS];             // P: slot (C head h / M head 8+h) x row
@@ -408,7 +412,7 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(2))) void h
   // both from LDS instead of waiting on two dependent loads per block.
   constexpr bool resolved = kResolved;
   constexpr int bit0 = resolved ? 16 : kPosBits;  // membership bits' position in an entry
-  uint16_t *const vrow = reinterpret_cast<uint16_t *>(sh.mem);
+  half_word_t *const vrow = reinterpret_cast<half_word_t *>(sh.mem);
 
   f32x4_t acc[kD / 16];
 #pragma unroll
@@ -481,7 +485,7 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(2))) void h
     int r1 = r0;
     {
       constexpr int kRows = kWin / kGT;  // most rows per wave
-      const uint16_t *const m16 = reinterpret_cast<const uint16_t *>(sh.mem) + r0 + lane;
+      const half_word_t *const m16 = reinterpret_cast<const half_word_t *>(sh.mem) + r0 + lane;
       uint32_t mb[kRows];
 #pragma unroll
       for (int i = 0; i < kRows; ++i) mb[i] = i < pc ? m16[i * kWave] : 0u;
@@ -499,7 +503,9 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(2))) void h
         c1 += ((mb[i] >> 12) * 0x204081u) & 0x01010101u;
       }
       // the wave's words are read: clear them for the next window (no other
-      // wave reads or sets them before the barrier that ends this one)
+      // wave reads or sets them before the barrier that ends this one).  A
+      // lane clears halves that other lanes read above
+      wave_lds_fence();
       for (int i = lane; i < pc * (kWave / 2); i += kWave) sh.mem[(r0 >> 1) + i] = 0u;
       uint32_t t[4] = {c0 & 0xff00ffu, (c0 >> 8) & 0xff00ffu, c1 & 0xff00ffu, (c1 >> 8) & 0xff00ffu};
 #pragma unroll
@@ -527,7 +533,7 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(2))) void h
           const int i = i0 + j * kWave + lane;
           if (i < r1) {
             sh.uni[i] = ((e[j] >> kPosBits) << 16) | (uint32_t)clampi(rk[j], 0, last_row);
-            vrow[i] = (uint16_t)clampi(rv[j], 0, last_row);
+            vrow[i] = (half_word_t)clampi(rv[j], 0, last_row);
           }
         }
       }
