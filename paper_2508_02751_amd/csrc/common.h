@@ -101,7 +101,7 @@ __device__ __forceinline__ Sizes set_sizes(const int32_t *seq_len, const int32_t
 __device__ __forceinline__ float cw_exp(float x) {
 #pragma clang fp contract(off)
   if (!(x >= -80.0f)) return 0.0f;
-  const float k = __builtin_rintf(__fmul_rn(x, 0x1.715476p+0f));
+  const float k = __builtin_rintf(x * 0x1.715476p+0f);
   float r = __builtin_fmaf(-k, 0x1.62e4p-1f, x);
   r = __builtin_fmaf(-k, 0x1.7f7d1cp-20f, r);
   float p = 0x1.a01a02p-13f;
@@ -121,12 +121,17 @@ constexpr float kUp = 0x1p64f, kDown = 0x1p-64f;
 
 // cw_exp(x) * 2^64, without a branch: x / ln 2 is rounded to an integer by
 // adding 1.5 * 2^23 (+ 64: even, so ties still go to even), whose low bits
-// then are the exponent to add to the polynomial's (0.7 .. 1.42).
+// then are the exponent to add to the polynomial's (0.7 .. 1.42).  The product
+// is rounded before the sum.  (HIP's __fmul_rn and __fadd_rn are plain
+// operators that its headers let the compiler contract, whatever this function
+// says: the two became one FMA, which rounds x / ln 2 within an ulp of a half
+// the other way.)
 __device__ __forceinline__ float exp_up(float x) {
 #pragma clang fp contract(off)
   constexpr float kMagic = 0x1.8p23f + 64.0f;
-  const float t = __fadd_rn(__fmul_rn(x, 0x1.715476p+0f), kMagic);
-  const float k = __fsub_rn(t, kMagic);
+  const float y = x * 0x1.715476p+0f;
+  const float t = y + kMagic;
+  const float k = t - kMagic;
   float r = __builtin_fmaf(-k, 0x1.62e4p-1f, x);
   r = __builtin_fmaf(-k, 0x1.7f7d1cp-20f, r);
   float p = 0x1.a01a02p-13f;
@@ -154,12 +159,12 @@ __device__ __forceinline__ Recip recip(float z) {
   Recip r;
   r.z = z;
   r.y = __fdiv_rn(1.0f, z);
-  r.dy = __fmul_rn(__builtin_fmaf(-r.y, z, 1.0f), r.y);
+  r.dy = __builtin_fmaf(-r.y, z, 1.0f) * r.y;
   return r;
 }
 __device__ __forceinline__ float div_by(float e, const Recip &r) {
 #pragma clang fp contract(off)
-  const float q = __builtin_fmaf(e, r.y, __fmul_rn(e, r.dy));
+  const float q = __builtin_fmaf(e, r.y, e * r.dy);
   return __builtin_fmaf(__builtin_fmaf(-q, r.z, e), r.y, q);
 }
 

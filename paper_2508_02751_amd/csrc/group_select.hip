@@ -89,8 +89,8 @@ __global__ __launch_bounds__(kGT) void group_zq(GroupSelArgs a) {
   for (int q = 0; q < kZqTok / kGT; ++q) {
     const int t = t0 + q * kGT + threadIdx.x;
     if (t < n) {
-      const float e = exp_up(__fsub_rn(lg[t], m));
-      z += (uint64_t)__float2ull_rz(__fmul_rn(e, 0x1p-24f));  // e * 2^40: exact scaling, truncation
+      const float e = exp_up(lg[t] - m);
+      z += (uint64_t)__float2ull_rz(e * 0x1p-24f);  // e * 2^40: exact scaling, truncation
     }
   }
   z = wave_sum_u64(z);
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kGT) void group_zq(GroupSelArgs a) {
 __device__ __forceinline__ float zq_of(const GroupSelArgs &a, int64_t row) {
   uint64_t z = 0;
   for (int c = 0; c < a.nzc; ++c) z += a.zq_int[row * a.nzc + c];
-  return __fmul_rn(__ull2float_rn(z), 0x1p-40f);
+  return __ull2float_rn(z) * 0x1p-40f;
 }
 
 // blockIdx.x: group row (b, layer, kv head); blockIdx.y: a chunk of
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kGT) void group_scores(GroupSelArgs a) {
     }
 #pragma unroll
     for (int q = 0; q < kQ; ++q)  // kQ independent chains; heads in ascending order
-      f[q] = __fadd_rn(f[q], prob_of(exp_up(__fsub_rn(x[q], m)), z));
+      f[q] = f[q] + prob_of(exp_up(x[q] - m), z);
   }
   float *out = a.keys + (int64_t)grow * a.n_cap;
   float fmx = 0.0f;
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kGT) void accum_scores(GroupSelArgs a) {
   for (int q = 0; q < kQ; ++q) {
     const int t = t0 + q * kGT + threadIdx.x;
     if (t < n) {
-      const float f = __fadd_rn(acc[t], prob_of(exp_up(__fsub_rn(lg[t], m)), z));
+      const float f = acc[t] + prob_of(exp_up(lg[t] - m), z);
       acc[t] = f;
       fmx = fmaxf(fmx, f);
     }

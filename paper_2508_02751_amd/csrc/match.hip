@@ -255,7 +255,7 @@ __device__ __forceinline__ void head_scores(const MatchArgs &a, const HeadsArgs 
         chunk(ch);
         float *p = s + own * pitch + min(ch * kCols + lane, pitch - 1);
 #pragma unroll
-        for (int i = 0; i < kOwn; ++i) p[i * pitch] = exp_up(__fsub_rn(e[i], mx[i]));
+        for (int i = 0; i < kOwn; ++i) p[i * pitch] = exp_up(e[i] - mx[i]);
       }
     }
     __syncthreads();
@@ -265,10 +265,10 @@ __device__ __forceinline__ void head_scores(const MatchArgs &a, const HeadsArgs 
       const float4 *row = reinterpret_cast<const float4 *>(s + lane * pitch);
       const int n4 = (r0 + nr + 3) / 4;
       auto add4 = [&](const float4 &e) {
-        z = __fadd_rn(z, e.x);
-        z = __fadd_rn(z, e.y);
-        z = __fadd_rn(z, e.z);
-        z = __fadd_rn(z, e.w);
+        z = z + e.x;
+        z = z + e.y;
+        z = z + e.z;
+        z = z + e.w;
       };
       int i = 0;
       for (; i + 4 <= n4; i += 4) {  // four reads in flight
@@ -297,11 +297,11 @@ __device__ __forceinline__ void head_scores(const MatchArgs &a, const HeadsArgs 
         }
         if (below && i + kBatch <= nr) {
 #pragma unroll
-          for (int q = 0; q < kBatch; ++q) f = __fadd_rn(f, p[q]);
+          for (int q = 0; q < kBatch; ++q) f = f + p[q];
         } else {
 #pragma unroll
           for (int q = 0; q < kBatch; ++q)
-            if (i + q < nr && col <= r0 + i + q) f = __fadd_rn(f, p[q]);
+            if (i + q < nr && col <= r0 + i + q) f = f + p[q];
         }
       }
     }

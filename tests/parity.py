@@ -145,3 +145,14 @@ def oracle_large_head(x, b, layer, h, part, mode, l_k=None, l_v=None, k_slot=Non
     return O.hybrid_head(host(l_q[b, layer, h]), host(l_k[b, layer, g]), host(l_v[b, layer, g]),
                          part["crit"], part["marg"], part["marg_prob"], part["mass"],
                          softmax_scale(d), mode, k_slot=ks, v_slot=vs)
+
+
+def exp32_half_points():
+    """Arguments of exp32 where x * fl(1/ln 2), rounded to fp32 before it is
+    rounded to an integer (the definition), and rounded once from the exact
+    product give different integers; at some of them the exponentials differ."""
+    c = np.float32(float.fromhex("0x1.715476p+0"))
+    mid = (-(np.arange(116) + 0.5) * np.log(2)).astype(np.float32).view(np.int32)
+    x = (mid[:, None] + np.arange(-40, 41, dtype=np.int32)).astype(np.int32).view(np.float32).ravel()
+    x = x[x >= -80]
+    return x[np.rint(x * c) != np.rint(x.astype(np.float64) * np.float64(c))]

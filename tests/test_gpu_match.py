@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import oracle as O
-from parity import host, log
+from parity import exp32_half_points, host, log
 
 pytestmark = pytest.mark.gpu
 
@@ -102,6 +102,31 @@ def test_window_edges(l_dtype, s_dtype):
             for t in ("q", "k"):
                 x[f"{name}_{t}"] = x[f"{name}_{t}"].to(torch.bfloat16)
     check_match(x, f"window edges, large {l_dtype}, small {s_dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_exponentials_at_half_integers(dtype):
+    """Logits at exp32's arguments where its integer part is decided by the
+    rounding of x / ln 2, below the first token's logit 0 (every row's
+    maximum); in bf16 each is the sum of three dims' products.  The small
+    model's logits are the points themselves (its scale is 1/8)."""
+    _, W, _, _ = lib_modules()
+    pts = exp32_half_points()
+    assert pts.size > 40
+    w = pts.size + 1
+    x = W.match_inputs(W.WORKLOADS[1], w, DEV)
+    for pre in ("l", "s"):
+        q, k = torch.zeros_like(x[f"{pre}_q"]), torch.zeros_like(x[f"{pre}_k"])
+        top = torch.from_numpy(pts.astype(np.float64) * np.sqrt(q.shape[-1])).to(DEV)
+        hi = top.float() if dtype == "f32" else top.to(torch.bfloat16).double()
+        parts = [hi] if dtype == "f32" else [hi, (top - hi).to(torch.bfloat16).double(),
+                                             top - hi - (top - hi).to(torch.bfloat16).double()]
+        for i, p in enumerate(parts):
+            q[..., i] = 1.0
+            k[..., 1:, i] = p.float()
+        dt = torch.float32 if dtype == "f32" else torch.bfloat16
+        x[f"{pre}_q"], x[f"{pre}_k"] = q.to(dt), k.to(dt)
+    check_match(x, f"exponentials at half integers {dtype}")
 
 
 def test_qwen2_7b_0_5b_window_200():

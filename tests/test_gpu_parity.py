@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import oracle as O
-from parity import compare_step, host, log, oracle_step
+from parity import compare_step, exp32_half_points, host, log, oracle_step
 from paper_2508_02751_amd import smallkv as S
 from paper_2508_02751_amd import workloads as W
 from paper_2508_02751_amd.pipeline import prepare_step
@@ -592,6 +592,47 @@ def test_accumulated_single_stage_calls_match_step():
     for got, want in ((acc, b.acc_score), (ci, b.crit_idx), (mi, b.marg_idx), (mp, b.marg_prob),
                       (ms, b.mass), (large.out, b.large_out)):
         assert torch.equal(got, want)
+
+
+def accum_rows(rows):
+    """smallkv_accum_select over crafted rows of logits [R][n] (row maximum
+    row[0]); returns the scores after one step from zero."""
+    R, n = rows.shape
+    lg = torch.from_numpy(rows).to(DEV).view(1, R, n).contiguous()
+    i32 = lambda v: torch.tensor([v], dtype=torch.int32, device=DEV)
+    batch = S.BatchSpec(i32(n), i32(2), i32(3), n, 2, 3)
+    q = torch.zeros((1, 1, R, 64), device=DEV)
+    kv = torch.zeros((1, 1, R, n, 64), device=DEV)
+    small = S.ModelSpec(q, kv, kv, torch.empty_like(q), 0.125)
+    rm, rs = lg[..., 0].contiguous(), torch.exp(lg - lg[..., :1]).sum(-1)
+    acc = torch.zeros_like(lg)
+    ci, mi = (torch.zeros((1, R, c), dtype=torch.int32, device=DEV) for c in (2, 3))
+    mp, ms = torch.zeros((1, R, 3), device=DEV), torch.zeros((1, R, 2), device=DEV)
+    ws = torch.empty(16 << 20, dtype=torch.uint8, device=DEV)
+    S.smallkv_accum_select(batch, small, lg, rm, rs, acc, ci, mi, mp, ms, ws)
+    torch.cuda.synchronize()
+    return host(acc)[0]
+
+
+def accum_scores_of(rows):
+    """The same scores by definition: exp32(row - max) / Z in fp32."""
+    out = []
+    for row in rows:
+        e = O.exp32(row - row[0])
+        out.append(e / O.zq(row, row[0]))
+    return np.stack(out)
+
+
+def test_accumulated_scores_at_exponentials_half_integers():
+    """Logits at exp32's arguments where its integer part is decided by the
+    rounding of x / ln 2, bit for bit."""
+    pts = exp32_half_points()
+    assert pts.size > 40
+    rows = np.concatenate([np.zeros(1, np.float32), pts])[None]
+    want = accum_scores_of(rows)
+    got = accum_rows(rows)
+    bad = got.view(np.uint32) != want.view(np.uint32)
+    assert not bad.any(), f"scores differ at {rows[bad]}"
 
 
 # ------------------------------------------- per-layer stage 3, step events --
