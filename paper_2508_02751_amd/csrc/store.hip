@@ -30,6 +30,7 @@ constexpr int kCT = 256;   // store_copy threads
 
 struct StoreArgs {
   int n_cap, layers, hq, hkv, g, nsh, kc_cap, km_cap, select, words;
+  int share;      // log2 of the store_index waves per query head
   int64_t rows;
   int row_bytes;  // head_dim * element size
   const int32_t *seq_len, *head_map, *crit, *marg;
@@ -69,78 +70,79 @@ __device__ __forceinline__ int32_t row_source(int os, int t, int64_t rows) {
   return (os >= 0 && os < rows) ? os : -(t + 1);
 }
 
-constexpr int kHeads = 8;
+constexpr int kIW = kIT / kWave;  // store_index waves
 
-// Sets the members of the lists of HB heads at `rows` (heads of them, the rest
-// skipped): IB entries of every head per thread and pass, all loads of a pass
-// in flight before any is used.  (A flat walk over all heads' entries, which
-// found each entry's head by a division and its row through the head map, and
-// old slots read one token at a time below, took 22 us for the index of a
-// Qwen2-7B step.)
-template <int HB, int IB>
-__device__ __forceinline__ void mark(const StoreArgs &a, const int64_t *rows, int heads, int n,
-                                     uint32_t *bk, uint32_t *bv) {
-  const int per = a.kc_cap + a.km_cap;
-  for (int i0 = threadIdx.x; i0 < per; i0 += IB * kIT) {
-    int tok[IB][HB];
+// The lists' row of query head h of a kv head (unit): its small head's, or the
+// unit's own with group selection.
+__device__ __forceinline__ int64_t list_row(const StoreArgs &a, int unit, int h) {
+  if (a.select) return unit;
+  const int kvh = unit % a.hkv, bl = unit / a.hkv, layer = bl % a.layers, b = bl / a.layers;
+  return (int64_t)b * a.nsh + clampi(a.head_map[layer * a.hq + kvh * a.g + h], 0, a.nsh - 1);
+}
+
+// Sets the members of the lists of a unit's query heads (-1 padding and
+// anything outside [0, n) ignored): critical tokens in bk, marginal ones in bv.
+// The waves are dealt to the heads, 1 << share of them each, so that a wave
+// finds its list's row once and without a barrier (`row`: its first head's).
+// The entries of a pass are all in flight before any is used; a list shorter
+// than the batch ends it early, on the scalar unit.  A first build of 8 layers
+// x 4 kv heads, groups of 4, 8 and 16: 9.2, 9.3 and 9.7 us at 600 tokens, 20.6,
+// 24.9 and 28.2 at 8192.  With the entries of up to eight heads per thread,
+// their rows handed over through LDS: 9.7, 9.9, 11.3 and 21.8, 26.1, 30.3.
+// With a flat walk that divides to find each entry's head: 9.2, 9.5, 9.8 and
+// 22.2, 27.8, 34.0.
+__device__ __forceinline__ void mark(const StoreArgs &a, int unit, int64_t row, int n, uint32_t *bk,
+                                     uint32_t *bv) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
+  const int per = a.kc_cap + a.km_cap, heads = a.select ? 1 : a.g;
+  const int step = kWave << a.share;
+  constexpr int kBatch = 4;
+  for (int h = wave >> a.share; h < heads;) {
+    const int32_t *crit = a.crit + row * a.kc_cap, *marg = a.marg + row * a.km_cap;
+    for (int base = (wave & ((1 << a.share) - 1)) * kWave; base < per; base += kBatch * step) {
+      int tok[kBatch];
 #pragma unroll
-    for (int q = 0; q < IB; ++q) {
-      const int i = i0 + q * kIT;
+      for (int q = 0; q < kBatch; ++q) {
+        if (base + q * step >= per) break;  // (uniform)
+        const int i = min(base + q * step + lane, per - 1);  // past the end: the last entry again
+        const int32_t *p = i < a.kc_cap ? crit + i : marg + (i - a.kc_cap);
+        tok[q] = *p;
+      }
 #pragma unroll
-      for (int h = 0; h < HB; ++h) {
-        tok[q][h] = -1;
-        if (h < heads && i < per)
-          tok[q][h] = i < a.kc_cap ? a.crit[rows[h] * a.kc_cap + i]
-                                   : a.marg[rows[h] * a.km_cap + (i - a.kc_cap)];
+      for (int q = 0; q < kBatch; ++q) {
+        if (base + q * step >= per) break;
+        const int i = min(base + q * step + lane, per - 1), t = tok[q];
+        if (t >= 0 && t < n) atomicOr(&(i < a.kc_cap ? bk : bv)[t >> 5], 1u << (t & 31));
       }
     }
-#pragma unroll
-    for (int q = 0; q < IB; ++q)
-#pragma unroll
-      for (int h = 0; h < HB; ++h) {
-        const int t = tok[q][h];
-        if (t >= 0 && t < n) {
-          if (i0 + q * kIT < a.kc_cap) atomicOr(&bk[t >> 5], 1u << (t & 31));
-          atomicOr(&bv[t >> 5], 1u << (t & 31));
-        }
-      }
+    h += kIW >> a.share;
+    if (h < heads) row = list_row(a, unit, h);
   }
 }
 
 __global__ __launch_bounds__(kIT) void store_index(StoreArgs a) {
   extern __shared__ uint32_t smem[];  // bits K [words], bits V [words], word ranks K, V
-  __shared__ int64_t rows[kHeads];    // the lists' rows of up to kHeads query heads
   uint32_t *bk = smem, *bv = smem + a.words;
   int *rk = reinterpret_cast<int *>(smem + 2 * a.words), *rv = rk + a.words;
   __shared__ int red[kIT / kWave];
   const int unit = blockIdx.x;
-  const int kvh = unit % a.hkv, bl = unit / a.hkv, layer = bl % a.layers, b = bl / a.layers;
+  const int b = unit / a.hkv / a.layers;
   const int n = clampi(a.seq_len[b], 1, a.n_cap);
   const int nw = (n + 31) / 32;
+  // the wave's first list, requested before the sequence's length is used
+  const int h0 = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) >> a.share;
+  const int64_t row0 = list_row(a, unit, min(h0, a.g - 1));
   for (int w = threadIdx.x; w < nw; w += kIT) bk[w] = bv[w] = 0u;
-  if (a.select) __syncthreads();  // (else the rows' barrier below)
+  __syncthreads();
   // membership from the lists of the group's query heads (one shared set
-  // per kv head with group selection); -1 padding and anything outside
-  // [0, n) ignored
-  if (a.select) {
-    const int64_t row = unit;
-    mark<1, 8>(a, &row, 1, n, bk, bv);
-  } else {
-    for (int h0 = 0; h0 < a.g; h0 += kHeads) {
-      const int heads = min(kHeads, a.g - h0);
-      if (h0 > 0) __syncthreads();  // the rows before are read
-      if ((int)threadIdx.x < heads)
-        rows[threadIdx.x] = (int64_t)b * a.nsh +
-                            clampi(a.head_map[layer * a.hq + kvh * a.g + h0 + (int)threadIdx.x], 0, a.nsh - 1);
-      __syncthreads();
-      mark<kHeads, 2>(a, rows, heads, n, bk, bv);
-    }
-  }
+  // per kv head with group selection)
+  mark(a, unit, row0, n, bk, bv);
   __syncthreads();
   // word ranks: each thread scans a run of consecutive words
   const int wper = (nw + kIT - 1) / kIT, w0 = threadIdx.x * wper, w1 = min(w0 + wper, nw);
   int ck = 0, cv = 0;
   for (int w = w0; w < w1; ++w) {
+    bv[w] |= bk[w];  // critical tokens keep their V rows too
     ck += __popc(bk[w]);
     cv += __popc(bv[w]);
   }
@@ -156,41 +158,48 @@ __global__ __launch_bounds__(kIT) void store_index(StoreArgs a) {
   __syncthreads();
   // slot maps and the rows' sources
   const int64_t sbase = (int64_t)unit * a.n_cap, ubase = (int64_t)unit * a.rows;
-  constexpr int kTok = 4;  // tokens per thread and pass, their old slots in flight together
-  for (int tb = threadIdx.x; tb < n; tb += kTok * kIT) {
-    int ock[kTok], ocv[kTok];
-#pragma unroll
-    for (int q = 0; q < kTok; ++q) {
-      const int t = tb + q * kIT;
-      ock[q] = ocv[q] = -1;
-      if (a.old_k && t < n) {
-        ock[q] = a.old_k_slot[sbase + t];
-        ocv[q] = a.old_v_slot[sbase + t];
+  auto place = [&](int t, int ock, int ocv) {  // token t, its rows in the old store
+    const uint32_t below = (1u << (t & 31)) - 1u;
+    const uint32_t wk = bk[t >> 5], wv = bv[t >> 5];
+    int sk = -1, sv = -1;
+    if (wk >> (t & 31) & 1u) {
+      const int r = rk[t >> 5] + __popc(wk & below);
+      if (r < a.rows) {
+        sk = r;
+        a.src_k[ubase + r] = row_source(ock, t, a.rows);
       }
     }
+    if (wv >> (t & 31) & 1u) {
+      const int r = rv[t >> 5] + __popc(wv & below);
+      if (r < a.rows) {
+        sv = r;
+        a.src_v[ubase + r] = row_source(ocv, t, a.rows);
+      }
+    }
+    a.k_slot[sbase + t] = sk;
+    a.v_slot[sbase + t] = sv;
+  };
+  if (!a.old_k) {
+    for (int t = threadIdx.x; t < n; t += kIT) place(t, -1, -1);
+  } else if (n <= kIT) {  // a token per thread
+    const int t = threadIdx.x;
+    if (t < n) place(t, a.old_k_slot[sbase + t], a.old_v_slot[sbase + t]);
+  } else {
+    constexpr int kTok = 4;  // tokens per thread and pass, their old slots in flight together
+    for (int tb = threadIdx.x; tb < n; tb += kTok * kIT) {
+      int ock[kTok], ocv[kTok];
 #pragma unroll
-    for (int q = 0; q < kTok; ++q) {
-      const int t = tb + q * kIT;
-      if (t >= n) break;
-      const uint32_t below = (1u << (t & 31)) - 1u;
-      const uint32_t wk = bk[t >> 5], wv = bv[t >> 5];
-      int sk = -1, sv = -1;
-      if (wk >> (t & 31) & 1u) {
-        const int r = rk[t >> 5] + __popc(wk & below);
-        if (r < a.rows) {
-          sk = r;
-          a.src_k[ubase + r] = row_source(ock[q], t, a.rows);
+      for (int q = 0; q < kTok; ++q) {
+        const int t = tb + q * kIT;
+        ock[q] = ocv[q] = -1;
+        if (t < n) {
+          ock[q] = a.old_k_slot[sbase + t];
+          ocv[q] = a.old_v_slot[sbase + t];
         }
       }
-      if (wv >> (t & 31) & 1u) {
-        const int r = rv[t >> 5] + __popc(wv & below);
-        if (r < a.rows) {
-          sv = r;
-          a.src_v[ubase + r] = row_source(ocv[q], t, a.rows);
-        }
-      }
-      a.k_slot[sbase + t] = sk;
-      a.v_slot[sbase + t] = sv;
+#pragma unroll
+      for (int q = 0; q < kTok; ++q)
+        if (tb + q * kIT < n) place(tb + q * kIT, ock[q], ocv[q]);
     }
   }
   if (threadIdx.x == 0) {
@@ -259,6 +268,8 @@ hipError_t launch_store_update(const smallkv_store_t &s, void *ws, hipStream_t s
   a.km_cap = s.batch.km_cap;
   a.select = s.select == SMALLKV_SELECT_GROUP ? 1 : 0;
   a.words = (s.batch.n_cap + 31) / 32;
+  // as many waves per head as leave none without (a power of two: no divisions)
+  while ((a.select ? 1 : a.g) << (a.share + 1) <= kIW) ++a.share;
   a.rows = s.rows;
   a.row_bytes = s.head_dim * (s.dtype == SMALLKV_F32 ? 4 : 2);
   a.seq_len = s.batch.seq_len;

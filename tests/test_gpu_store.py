@@ -100,7 +100,7 @@ def test_store_from_a_step(select, dtype):
 
 @pytest.mark.parametrize("g", [1, 8, 9, 16])
 def test_store_group_sizes(g):
-    """Lists are marked eight heads at a time: one pass full, part of one, two."""
+    """Sixteen waves mark the lists: all of them one head's, two and one per head."""
     S, W, prepare_step = modules()
     w = W.Workload(136, f"store-g{g}", 2, 1300, "bf16", W.ModelShape(2, 8, 2, 64),
                    W.ModelShape(2, 2 * g, 2, 128), ("pct", 8), ("pct", 15), ragged_min=500)
@@ -114,6 +114,36 @@ def test_store_group_sizes(g):
     sc.run()
     torch.cuda.synchronize()
     check_store(sc, oracle_store(x, ps, rows, 0), x, f"store, groups of {g}")
+
+
+@pytest.mark.parametrize("g,n", [(3, 1023), (5, 1024), (7, 70), (17, 1025), (33, 4100)])
+def test_store_waves_dealt_to_heads(g, n):
+    """Groups that leave waves idle or need several rounds of them; lists shorter
+    than a wave; lengths around a token per index thread.  First build, then an
+    update from that store, altered so that its rows show in the result."""
+    S, W, prepare_step = modules()
+    w = W.Workload(137, f"store-deal{g}", 1, n, "bf16", W.ModelShape(1, 8, 2, 64),
+                   W.ModelShape(1, 2 * g, 2, 128), ("pct", 8), ("pct", 15))
+    x = W.make_step_inputs(w, DEV)
+    ps = prepare_step(x)
+    ps.run()
+    rows = capacity(x, g)
+
+    def build(old=None):
+        sc = S.prepare_store(ps.batch, ps.head_map, ps.buf.logits.shape[1], ps.buf.crit_idx,
+                             ps.buf.marg_idx, x["l_k"], x["l_v"], rows, old=old)
+        log(f"[store] groups of {g}, {n} tokens, old store {old is not None}")
+        sc.run()
+        torch.cuda.synchronize()
+        return sc
+
+    first = build()
+    ref = oracle_store(x, ps, rows, 0)
+    check_store(first, ref, x, f"store, groups of {g}, {n} tokens")
+    first.new_k += 1.0
+    first.new_v -= 1.0
+    ref = (host(first.new_k), host(first.new_v)) + ref[2:]  # every row comes from the old store
+    check_store(build(first), ref, x, f"store update, groups of {g}, {n} tokens")
 
 
 def test_store_reuses_the_previous_store_across_steps():
