@@ -2,6 +2,7 @@
 oracle: the Eq. 1 scores bit for bit, the TopK sets and the head map exactly."""
 from __future__ import annotations
 
+import ctypes
 import dataclasses
 
 import numpy as np
@@ -127,6 +128,73 @@ def test_exponentials_at_half_integers(dtype):
         dt = torch.float32 if dtype == "f32" else torch.bfloat16
         x[f"{pre}_q"], x[f"{pre}_k"] = q.to(dt), k.to(dt)
     check_match(x, f"exponentials at half integers {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("w,k", [(40, 5), (150, 40), (256, 256)])
+def test_infinite_and_subnormal_logits(dtype, w, k):
+    """Heads with a +inf logit in one row (that row's weights, and with them the
+    sums of its tokens, are NaN: ranked above nothing and below nothing, so in),
+    with a -inf logit, and with subnormal products; scores bit for bit."""
+    S, _, _, _ = lib_modules()
+    d, g, rng = 64, 4, np.random.default_rng(w)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def model(bad_row):
+        q = torch.from_numpy(rng.standard_normal((1, 1, g, w, d)).astype(np.float32))
+        key = torch.from_numpy(rng.standard_normal((1, 1, g, w, d)).astype(np.float32))
+        q[..., 0] = 0.0
+        q[:, :, 0, bad_row, 0], key[:, :, 0, 3, 0] = 2.0 ** 100, 2.0 ** 100    # +inf
+        q[:, :, 1, bad_row, 0], key[:, :, 1, 3, 0] = 2.0 ** 100, -2.0 ** 100   # -inf
+        q[:, :, 2] *= 2.0 ** -70                                              # subnormal products
+        key[:, :, 2] *= 2.0 ** -66
+        return q.to(dt), key.to(dt)
+
+    lq, lk = model(w // 2)
+    sq, sk = model(w // 3)
+    i32 = lambda v: torch.tensor([v], dtype=torch.int32, device=DEV)
+    mc = S.prepare_match(i32(w), i32(k), lq.to(DEV), lk.to(DEV), 0.125, sq.to(DEV), sk.to(DEV), 0.125)
+    log(f"[match] infinite and subnormal logits, window {w} {dtype}")
+    mc.run()
+    torch.cuda.synchronize()
+    F, top = [], []
+    for q, key in ((lq, lk), (sq, sk)):
+        for h in range(g):
+            F.append(sums(q[0, 0, h].float().numpy(), key[0, 0, h].float().numpy(), 0.125))
+            f = F[-1]
+            above = (f[None] > f[:, None]) | ((f[None] == f[:, None]) & (np.arange(w)[None] < np.arange(w)[:, None]))
+            top.append(above.sum(1) < k)
+    F, top = np.stack(F), np.stack(top)
+    nan = np.isnan(F)
+    assert nan[0, : w // 2 + 1].all() and not nan[0, w // 2 + 1:].any() and not nan[1:g].any()
+    got = host(mc.scores)[0]
+    assert np.array_equal(np.isnan(got), nan)
+    assert not ((got.view(np.uint32) != F.view(np.uint32)) & ~nan).any(), "scores differ"
+    assert np.array_equal(unpack_bits(host(mc.top_bits)[0], w), top), "TopK sets differ"
+    for i in range(g):
+        share = [(top[i] & t).sum() / (top[i] | t).sum() for t in top[g:]]
+        assert int(mc.head_map[0, i]) == int(np.argmax(share))
+
+
+def sums(q, k, scale):
+    """F of Eq. 1 of one head by its definition, infinite logits included."""
+    w = q.shape[0]
+    f = O.lib().orc_logit
+    f.restype = ctypes.c_float
+    P = ctypes.POINTER(ctypes.c_float)
+    f.argtypes = [ctypes.c_int, ctypes.c_float, P, P]
+    q, k = np.ascontiguousarray(q), np.ascontiguousarray(k)
+    F = np.zeros(w, np.float32)
+    with np.errstate(invalid="ignore"):
+        for u in range(w):
+            s = np.array([f(q.shape[1], scale, q[u].ctypes.data_as(P), k[v].ctypes.data_as(P))
+                          for v in range(u + 1)], np.float32)
+            e = O.exp32(s - s.max())
+            z = np.float32(0)
+            for x in e:
+                z = z + x
+            F[: u + 1] = F[: u + 1] + e / z
+    return F
 
 
 def test_qwen2_7b_0_5b_window_200():

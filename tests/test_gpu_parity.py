@@ -1,6 +1,7 @@
 """GPU parity: the library (through the C ABI) against the CPU oracle on the
 same seeded inputs.  Index sets and logits bit-exact, outputs within the
 per-dtype tolerance of tests/parity.py."""
+import ctypes
 import dataclasses
 
 import numpy as np
@@ -475,9 +476,9 @@ def test_group_selection_ragged_with_recent_tokens():
 
 
 def test_group_selection_of_tiny_probabilities():
-    """Queries 4x scaled: about half of a row's exponentials are below 2^-94,
-    where quotients could be subnormal, and a third are zero; the budgets take
-    in both ranges."""
+    """Queries 4x scaled: about half of a row's exponentials are below 2^-94 and
+    a third are zero; the budgets take in both ranges.  (Lists only, of normal
+    quotients: Z stays below 2.  Subnormal ones: the tests after the next.)"""
     w = custom("gsel-tiny", 124, 2, 1100, "bf16", SMALL, LARGE, ("pct", 40), ("pct", 40))
 
     def spread(x):
@@ -633,6 +634,163 @@ def test_accumulated_scores_at_exponentials_half_integers():
     got = accum_rows(rows)
     bad = got.view(np.uint32) != want.view(np.uint32)
     assert not bad.any(), f"scores differ at {rows[bad]}"
+
+
+def subnormal_quotient_row(n_top=130001, n_low=10000, seed=5):
+    """Logits whose quotients exp32 / Z are subnormal in the tail: n_top tokens at
+    the maximum 0 make Z = n_top; n_low tokens hold the fp32 numbers from -80 up,
+    whose quotients are less than a step apart, n_low more lie between -76 and -80.
+    Returns (logits, quotients by definition, quotients rounded twice: first at
+    2^64 times their size)."""
+    rng = np.random.default_rng(seed)
+    near = (np.float32(-80).view(np.int32) - np.arange(n_low, dtype=np.int32)).view(np.float32)
+    low = np.concatenate([near, rng.uniform(-80, -76, n_low).astype(np.float32)])
+    row = np.zeros(n_top + low.size, np.float32)
+    row[1 + rng.permutation(row.size - 1)[: low.size]] = low
+    e = O.exp32(row)
+    z = O.zq(row, 0.0)
+    assert z == n_top
+    twice = (e * np.float32(2.0 ** 64) / z) * np.float32(2.0 ** -64)
+    return row, e / z, twice
+
+
+def test_accumulated_scores_of_subnormal_quotients():
+    """Quotients below 2^-126 are rounded once."""
+    row, want, twice = subnormal_quotient_row()
+    tiny = np.finfo(np.float32).tiny
+    low = (want > 0) & (want < tiny)
+    assert low.sum() > 100 and (want[low] != twice[low]).any()
+    got = accum_rows(row[None])[0]
+    bad = got.view(np.uint32) != want.view(np.uint32)
+    assert not bad.any(), f"{int(bad.sum())} scores differ"
+
+
+def test_group_selection_ranks_subnormal_quotients():
+    """One query head per kv head, budgets that end between two tokens whose keys
+    a second rounding of the quotient would tie or exchange."""
+    row, key, twice = subnormal_quotient_row()
+    n, n_top = row.size, int((row == 0).sum())
+
+    def ranked(k):
+        return np.lexsort((np.arange(n), -k.astype(np.float64)))
+
+    right, wrong = ranked(key), ranked(twice)
+    at = np.nonzero(right != wrong)[0]
+    ends = [int(k) + 1 for k in at if k > n_top and set(right[n_top:k + 1]) != set(wrong[n_top:k + 1])]
+    assert ends
+    i32 = lambda v: torch.tensor([v], dtype=torch.int32, device=DEV)
+    for nc in ends[:3]:
+        nm = n - nc - 1
+        batch = S.BatchSpec(i32(n), i32(nc), i32(nm), n, nc, nm)
+        spec = []
+        for d in (64, 128):
+            q = torch.zeros((1, 1, 1, d), dtype=torch.bfloat16, device=DEV)
+            kv = torch.zeros((1, 1, 1, n, d), dtype=torch.bfloat16, device=DEV)
+            spec.append(S.ModelSpec(q, kv, kv, torch.empty_like(q), 0.125))
+        lg = torch.from_numpy(row).to(DEV).view(1, 1, n)
+        rm, rs = torch.zeros((1, 1), device=DEV), torch.exp(lg).sum(-1)
+        ci, mi = (torch.full((1, 1, c), -2, dtype=torch.int32, device=DEV) for c in (nc, nm))
+        mp, ms = torch.zeros((1, 1, nm), device=DEV), torch.zeros((1, 1, 2), device=DEV)
+        ws = torch.empty(16 << 20, dtype=torch.uint8, device=DEV)
+        S.smallkv_group_select(batch, spec[0], spec[1], torch.zeros(1, dtype=torch.int32, device=DEV),
+                               lg, rm, rs, ci, mi, mp, ms, ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(ci)[0, 0], np.sort(right[:nc])), f"critical tokens, {nc}"
+        assert np.array_equal(host(mi)[0, 0], np.sort(right[nc:nc + nm])), f"marginal tokens, {nc}"
+
+
+# ------------------------------------------------------------ special values --
+
+def special_operands(d, heads, dtype, seed=7):
+    """q [heads][d] and k [tokens][d] (fp32 values that dtype holds) whose products
+    and partial sums are subnormal, cancel, overflow, or meet infinities and NaN."""
+    rng = np.random.default_rng(seed)
+
+    def rnd(scale, *shape):
+        return (rng.standard_normal(shape) * scale).astype(np.float32)
+
+    q = np.stack([(rnd(1, d), rnd(2.0 ** -75, d), rnd(2.0 ** 60, d), rnd(2.0 ** -140, d),
+                   np.where(np.arange(d) % 2, 0.0, -0.0).astype(np.float32))[h % 5] for h in range(heads)])
+    rows = []
+    for _ in range(12):
+        rows += [rnd(1, d), rnd(2.0 ** -70, d), rnd(2.0 ** -138, d), rnd(2.0 ** 70, d), rnd(2.0 ** 124, d)]
+        x = rnd(1, d // 2)
+        rows.append(np.repeat(x, 2) * np.tile(np.float32([1, -1]), d // 2))  # cancels against equal dims
+        rows.append(np.zeros(d, np.float32) * (-1) ** len(rows))
+        for v in (np.inf, -np.inf, np.nan):
+            y = rnd(1, d)
+            y[rng.integers(d)] = v
+            rows.append(y)
+        y = rnd(1, d)
+        y[rng.permutation(d)[:2]] = (np.inf, -np.inf)
+        rows.append(y)
+    q[0, 1::2] = q[0, ::2]
+    k = np.stack(rows)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    return (torch.from_numpy(v.astype(np.float32)).to(t) for v in (q, k))
+
+
+def oracle_logits(q, k, scale):
+    """[heads][tokens], each the sequential FMA chain."""
+    f = O.lib().orc_logit
+    f.restype = ctypes.c_float
+    P = ctypes.POINTER(ctypes.c_float)
+    f.argtypes = [ctypes.c_int, ctypes.c_float, P, P]
+    q, k = (np.ascontiguousarray(v.float().numpy()) for v in (q, k))
+    return np.array([[f(q.shape[1], scale, a.ctypes.data_as(P), b.ctypes.data_as(P)) for b in k] for a in q],
+                    np.float32)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,g", [(64, 3), (64, 7), (64, 16), (128, 4), (128, 8), (128, 9)])
+def test_logits_of_special_values(dtype, d, g):
+    """Stage 1's logits bit for bit where products and partial sums are subnormal,
+    cancel or overflow; infinities and NaN where the chain gives them."""
+    q, k = special_operands(d, g, dtype)
+    n = k.shape[0]
+    want = oracle_logits(q, k, 0.125)
+    tiny = np.finfo(np.float32).tiny
+    assert ((want != 0) & (np.abs(want) < tiny)).any() and np.isinf(want).any() and np.isnan(want).any()
+    one = torch.ones(1, dtype=torch.int32, device=DEV)
+    batch = S.BatchSpec(one * n, one, one, n, 1, 1)
+    kv = k.to(DEV).view(1, 1, 1, n, d).contiguous()
+    qd = q.to(DEV).view(1, 1, g, d).contiguous()
+    small = S.ModelSpec(qd, kv, torch.zeros_like(kv), torch.empty_like(qd), 0.125)
+    lg = torch.zeros((1, g, n), device=DEV)
+    rm, rs = torch.zeros((1, g), device=DEV), torch.zeros((1, g), device=DEV)
+    ws = torch.empty(16 << 20, dtype=torch.uint8, device=DEV)
+    log(f"[special] stage 1 {dtype} d {d} g {g}")
+    S.smallkv_small_attn(batch, small, lg, rm, rs, ws)
+    torch.cuda.synchronize()
+    got = host(lg)[0]
+    assert np.array_equal(np.isnan(got), np.isnan(want)), "NaN logits"
+    ok = ~np.isnan(want)
+    bad = ok & (got.view(np.uint32) != want.view(np.uint32))
+    assert not bad.any(), f"{int(bad.sum())} logits differ, e.g. {got[bad][:4]} for {want[bad][:4]}"
+
+
+@pytest.mark.parametrize("small,batch,n", [((2, 8, 2), 1, 900), ((24, 14, 2), 1, 700), ((4, 16, 4), 16, 800),
+                                           ((4, 16, 4), 16, 6000)])
+def test_infinite_logits_rank_exactly(small, batch, n):
+    """-inf logits rank last (by index), one +inf first: lists and row maxima of
+    1024-, 512- and 256-thread rows, in registers and re-read."""
+    w = custom(f"inf-{n}-{batch}", 141, batch, n, "bf16", W.ModelShape(*small, 64), W.ModelShape(1, 8, 2, 128),
+               ("pct", 30), ("pct", 68))
+    x = W.make_step_inputs(w, DEV)
+    x["s_q"][..., 0] = 1.0
+    x["s_k"][..., 5::7, 0] = -float("inf")
+    x["s_k"][:, :, 0, n // 2, 0] = float("inf")
+    ps = prepare_step(x)
+    log(f"[special] infinite logits, {small} batch {batch} n {n}")
+    ps.run()
+    torch.cuda.synchronize()
+    lg = host(ps.buf.logits).reshape(-1, n)
+    assert np.isneginf(lg).any() and np.isposinf(lg).any() and not np.isnan(lg).any()
+    assert np.array_equal(host(ps.buf.row_max).ravel(), lg.max(1))
+    nc, nm = int(x["k_crit"][0]), int(x["k_marg"][0])
+    order = np.argsort(-lg, axis=1, kind="stable")
+    assert np.array_equal(host(ps.buf.crit_idx).reshape(-1, nc), np.sort(order[:, :nc], 1))
+    assert np.array_equal(host(ps.buf.marg_idx).reshape(-1, nm), np.sort(order[:, nc:nc + nm], 1))
 
 
 # ------------------------------------------- per-layer stage 3, step events --
