@@ -182,7 +182,9 @@ int smallkv_partition(const smallkv_batch_t *batch, const smallkv_model_t *small
  *   s_t = scale * <q, K_g[row(t)]> for t in crit_idx[b][j]
  *   O_c = sum_C softmax_C(s)_t V_g[row(t)],  O_m = sum_M marg_prob_t V_g[row(t)]
  *   large->out = alpha_C * O_c + alpha_M * O_m   (alphas from `mode` and mass[b][j])
- * head_map: [n_layers * n_q_heads] int32 (device).  Rows come from
+ * head_map: [n_layers * n_q_heads] int32 (device).  Lists have the sizes of
+ * smallkv_batch_t, or end before them in -1 (a small model that holds fewer
+ * rows than the budgets ask for).  Rows come from
  * large->k_slot / v_slot when given.  select = SMALLKV_SELECT_GROUP: the
  * lists are those of the large head's (layer, kv head) and marg_prob / mass
  * its own (the layouts of smallkv_group_select). */

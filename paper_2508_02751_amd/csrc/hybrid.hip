@@ -132,11 +132,15 @@ __global__ __launch_bounds__(kHT) void hybrid_kernel(HybArgs a) {
   float lmax = -INFINITY;
   for (int base = wave * BE; base < nc; base += kNW * BE) {
     const int my = base + lane;
-    int r = 0;
+    int r = 0, e = -1;
     if (lane < BE && my < nc) {
-      const int t = clampi(crit[my], 0, a.n_cap - 1);
+      e = crit[my];
+      const int t = clampi(e, 0, a.n_cap - 1);
       r = clampi(ks ? ks[t] : t, 0, last_row);
+      // a list cut short by the small model's held rows ends in -1
+      if (e < 0) s_crit[my] = -INFINITY;
     }
+    const int end = base + __popcll(__builtin_amdgcn_ballot_w64(e >= 0));  // of the block's tokens
     uint4 w[NS];
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
@@ -152,7 +156,7 @@ __global__ __launch_bounds__(kHT) void hybrid_kernel(HybArgs a) {
       for (int e = 0; e < EPL; ++e) d = __builtin_fmaf(qv[e], kv[e], d);
       d = row_reduce<LPR>(d);
       const int i = base + k * RPW + rg;
-      if (i < nc) {
+      if (i < end) {
         const float s = d * a.scale;
         if (sub == 0) s_crit[i] = s;
         lmax = fmaxf(lmax, s);

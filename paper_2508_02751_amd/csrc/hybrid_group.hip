@@ -221,6 +221,11 @@ __device__ __forceinline__ ListRef list_ref(const GroupArgs &a, const GroupShare
   return r;
 }
 
+// An entry's token, with the -1 of a list's padding after every token: a list
+// that the small model's held rows cut short ends in padding before the
+// length the budgets give.
+__device__ __forceinline__ bool token_before(int entry, int target) { return (uint32_t)entry < (uint32_t)target; }
+
 // First position of every list holding a token >= target (the lists are
 // ascending).  The wave runs one 64-way search per list, all lists in
 // lockstep so that their loads overlap: probes split [lo, hi) into 64
@@ -250,7 +255,7 @@ __device__ __forceinline__ void lower_bounds(const ListRef (&l)[kLPW], int targe
     for (int i = 0; i < kLPW; ++i) {
       const int span = hi[i] - lo[i];
       if (span > kWave) {
-        const int c = __popcll(__ballot(v[i] < target));
+        const int c = __popcll(__ballot(token_before(v[i], target)));
         const int nlo = c > 0 ? lo[i] + (int)(((int64_t)(c - 1) * span) >> 6) + 1 : lo[i];
         const int nhi = c < kWave ? lo[i] + (int)(((int64_t)c * span) >> 6) : hi[i];
         lo[i] = nlo;
@@ -262,7 +267,7 @@ __device__ __forceinline__ void lower_bounds(const ListRef (&l)[kLPW], int targe
   for (int i = 0; i < kLPW; ++i) {
     const int q = lo[i] + lane;
     const int v = q < hi[i] ? l[i].p[q] : INT_MAX;
-    res[i] = lo[i] + __popcll(__ballot(v < target));
+    res[i] = lo[i] + __popcll(__ballot(token_before(v, target)));
   }
 }
 
@@ -453,7 +458,7 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(2))) void h
           int cnt = 0;
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const bool in = e[i][k] < we;
+            const bool in = token_before(e[i][k], we);
             if (in && e[i][k] >= ws) {
               const int p = e[i][k] - ws;
               atomicOr(&sh.mem[p >> 1], lists[i].bit << (16 * (p & 1)));

@@ -210,6 +210,19 @@ def test_evicted_small_cache_ragged_with_recent(dtype):
     run_case(w)
 
 
+@pytest.mark.parametrize("dtype,g,crit,marg,recent,n", [
+    ("bf16", 4, 60, 40, 0, 1412), ("bf16", 1, 20, 30, 0, 2500), ("bf16", 8, 45, 10, 0, 5000),
+    ("bf16", 16, 60, 40, 0, 200), ("f32", 4, 45, 10, 0, 3000), ("f32", 2, 30, 30, 20, 700)])
+def test_evicted_small_cache_with_fewer_rows_than_the_budgets(dtype, g, crit, marg, recent, n):
+    """40% of the tokens held and budgets beyond that: the lists end in padding
+    before the lengths that stage 3 takes from the budgets."""
+    kw = {"recent": ("pct", recent)} if recent else {}
+    w = custom(f"slm-short-{n}", 142, 2, n, dtype, W.ModelShape(2, 8, 2, 64), W.ModelShape(2, 2 * g, 2, 128),
+               ("pct", crit), ("pct", marg), slm_keep=40, **kw)
+    ps, _, _ = run_case(w)
+    assert (host(ps.buf.marg_idx)[..., -1] == -1).all()
+
+
 def test_recent_window_with_ties():
     w = custom("recent-ties", 120, 2, 1500, "bf16", SMALL, LARGE, ("pct", 10), ("pct", 25),
                recent=("pct", 5))
