@@ -448,8 +448,12 @@ typedef struct {
                                set iff token v is in the head's TopK set */
 } smallkv_match_t;
 
-/* Bytes of workspace smallkv_match needs: two fp32 [B][H][w_cap][w_cap]
- * logit matrices plus the TopK bitsets.  Host only. */
+/* Bytes of workspace smallkv_match asks for: with w4 = w_cap rounded up to 4 and
+ * nw = ceil(w_cap / 64), the fp32 arrays [B][H][w_cap][w4], [B][H][w_cap][nw] and
+ * [B][H][w_cap][2], each rounded up to 256 bytes, and the TopK bitsets
+ * [B][H][nw] of 8 bytes.  Only the bitsets, at its start, are used: the logits
+ * stay on chip.  The size is kept for callers that hold a workspace; a smaller
+ * one gives SMALLKV_EWORKSPACE.  Host only. */
 int smallkv_match_workspace_size(const smallkv_match_t *match, size_t *bytes);
 
 /* Enqueues the matching on `stream` (two or three kernel launches). */

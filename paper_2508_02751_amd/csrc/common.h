@@ -94,38 +94,20 @@ __device__ __forceinline__ Sizes set_sizes(const int32_t *seq_len, const int32_t
   return s;
 }
 
-// exp(x), x <= 0: k = rne(x * fl(1/ln 2)); r = x - k*ln2 in two FMAs with ln2
-// split into a 16-bit head and a tail; e^r from the Taylor polynomial of
+// Probabilities come from exponentials scaled by 2^64 (exact: e is 0 or 2^-116
+// .. 1), so that no remainder of the divisions below is subnormal.
+constexpr float kDown = 0x1p-64f;
+
+// exp(x) * 2^64, x <= 0: k = rne(x * fl(1/ln 2)); r = x - k*ln2 in two FMAs with
+// ln2 split into a 16-bit head and a tail; e^r from the Taylor polynomial of
 // degree 7 by Horner's rule (coefficients 1/n! rounded to fp32); the result
-// scaled by 2^k exactly.  0 below -80, so no result is subnormal.
-__device__ __forceinline__ float cw_exp(float x) {
-#pragma clang fp contract(off)
-  if (!(x >= -80.0f)) return 0.0f;
-  const float k = __builtin_rintf(x * 0x1.715476p+0f);
-  float r = __builtin_fmaf(-k, 0x1.62e4p-1f, x);
-  r = __builtin_fmaf(-k, 0x1.7f7d1cp-20f, r);
-  float p = 0x1.a01a02p-13f;
-  p = __builtin_fmaf(p, r, 0x1.6c16c2p-10f);
-  p = __builtin_fmaf(p, r, 0x1.111112p-7f);
-  p = __builtin_fmaf(p, r, 0x1.555556p-5f);
-  p = __builtin_fmaf(p, r, 0x1.555556p-3f);
-  p = __builtin_fmaf(p, r, 0.5f);
-  p = __builtin_fmaf(p, r, 1.0f);
-  p = __builtin_fmaf(p, r, 1.0f);
-  return ldexpf(p, (int)k);
-}
-
-// Probabilities from exponentials scaled by 2^64 (exact: e is 0 or 2^-116 ..
-// 1), so that no remainder of the divisions below is subnormal.
-constexpr float kUp = 0x1p64f, kDown = 0x1p-64f;
-
-// cw_exp(x) * 2^64, without a branch: x / ln 2 is rounded to an integer by
-// adding 1.5 * 2^23 (+ 64: even, so ties still go to even), whose low bits
-// then are the exponent to add to the polynomial's (0.7 .. 1.42).  The product
-// is rounded before the sum.  (HIP's __fmul_rn and __fadd_rn are plain
-// operators that its headers let the compiler contract, whatever this function
-// says: the two became one FMA, which rounds x / ln 2 within an ulp of a half
-// the other way.)
+// scaled by 2^(k + 64) exactly.  0 below -80, so that exp(x) is never subnormal.
+// Without a branch: x / ln 2 is rounded to an integer by adding 1.5 * 2^23 (+ 64:
+// even, so ties still go to even), whose low bits then are the exponent to add
+// to the polynomial's (0.7 .. 1.42).  The product is rounded before the sum.
+// (HIP's __fmul_rn and __fadd_rn are plain operators that its headers let the
+// compiler contract, whatever this function says: the two became one FMA, which
+// rounds x / ln 2 within an ulp of a half the other way.)
 __device__ __forceinline__ float exp_up(float x) {
 #pragma clang fp contract(off)
   constexpr float kMagic = 0x1.8p23f + 64.0f;

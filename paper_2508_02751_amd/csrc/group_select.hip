@@ -4,7 +4,7 @@
 // selection of the implementation pseudocode (Appendix D, `.sum.topk`).
 //
 // The sum decides integers, so it has one defined evaluation (smallkv.h):
-//   e_j(t) = cw_exp(s_j(t) - m_j)                        (fp32)
+//   e_j(t) = exp32(s_j(t) - m_j)                         (fp32)
 //   Zq_j   = sum_t floor(e_j(t) * 2^40), an exact integer (any order)
 //   Z_j    = fp32(Zq_j) * 2^-40
 //   F(t)   = ((e_j0/Z_j0 + e_j1/Z_j1) + ...)               (fp32, heads ascending)

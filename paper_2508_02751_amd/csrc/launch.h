@@ -116,7 +116,7 @@ size_t store_workspace(const smallkv_store_t &s);
 hipError_t launch_store_update(const smallkv_store_t &s, void *ws, hipStream_t st);
 
 // Workspace of the prefill matching: the TopK bitsets ([B][H][nw] words of 64
-// tokens); total is the size the header states.
+// tokens) at its start; total is the size callers are asked for.
 struct MatchLayout {
   int nw;
   size_t total;

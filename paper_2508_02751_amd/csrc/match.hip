@@ -18,8 +18,8 @@
 //                  each row's maximum and exponentials, its sum Z_u (v
 //                  ascending), and every column's sum F_v (one thread per
 //                  token, u ascending over the row blocks) in a register;
-//                  then the TopK set by counting, for each token, the tokens
-//                  ranked above it;
+//                  then the TopK set by one wave, which finds the k-th largest
+//                  sum bit by bit;
 //   match_map   -- one wave per large head: Jaccard ratios against every
 //                  small head from TopK bitsets (popcounts), the argmax by
 //                  exact cross-multiplication, ties to the lowest small head.
@@ -142,12 +142,13 @@ __device__ __forceinline__ float wave_max8(float (&v)[8]) {
   return dpp_max<0x141>(x); // 8-lane mirror
 }
 
-// Exponentials, and with them Z and F, are held scaled by 2^64 (kUp: exact, as
+// Exponentials, and with them Z and F, are held scaled by 2^64 (exact, as
 // none of them is ever subnormal or near overflow: e is 0 or 2^-116 .. 1), so
 // that no remainder of the divisions is subnormal.
 // LDS of a workgroup (floats): the pass's logits [kRows][pitch], then Z and
-// its reciprocal per row.  The column sums take the logits' place at the end.  The pitch follows the window capacity, so that
-// five workgroups of 200-token windows fit a CU.
+// its reciprocal per row.  The column sums take the logits' place at the end.
+// The pitch follows the window capacity, so that five workgroups of 200-token
+// windows fit a CU.
 __host__ __device__ constexpr int pitch_of(int w_cap) { return (w_cap + 3) / 4 * 4 + 4; }
 constexpr size_t heads_lds(int w_cap) {
   const size_t f = (size_t)kRows * pitch_of(w_cap);
@@ -452,8 +453,9 @@ MatchLayout match_layout(const smallkv_match_t &m) {
   const int64_t H = (int64_t)m.large.n_layers * m.large.n_q_heads +
                     (int64_t)m.small.n_layers * m.small.n_q_heads;
   l.nw = (m.w_cap + kWave - 1) / kWave;
-  // the size the header states: the logits stay in LDS, only the bitsets at
-  // the start are used
+  // Only the bitsets at the start are used (the logits stay in LDS).  The size
+  // is that of one logit matrix, its tile maxima and row statistics before them,
+  // as callers that keep a workspace were told.
   auto round256 = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t rows = (size_t)m.batch * H * m.w_cap, ld = (m.w_cap + 3) / 4 * 4, nt = l.nw;
   l.total = round256(rows * ld * sizeof(float)) + round256(rows * nt * sizeof(float)) +

@@ -29,9 +29,10 @@
 // flight, the candidate gather from the row's end (it starts on what the
 // histogram pass read last).  Many rows (several per CU) get 256 threads
 // each, so that more rows are resident (six per CU); few rows
-// get 512, or 1024 when there is at most one per CU.  The fused variant
-// first combines stage 1's per-chunk records of its head (row max, row sum,
-// the head's output), so a step needs no separate merge launch.
+// get 512, or 1024 when there is at most one per CU.  The fused variant takes
+// the row's max from stage 1's per-chunk records first and combines them (row
+// sum, the head's output) beside the select, so a step needs no separate merge
+// launch.
 // The result depends only on the logits: deterministic.
 #include "common.h"
 #include "launch.h"
@@ -44,7 +45,7 @@ namespace {
 // GPU, 512 or 1024 when a few rows must finish fast)
 constexpr int kBins = 2048;
 // With 512 or more threads per row, histograms keep 16 bytes of padding
-// after every 32 bins: find_digit's lanes each read 32 consecutive bins, and
+// after every 32 bins: find_digits' lanes each read 32 consecutive bins, and
 // the 144-byte stride between lanes puts the 16 lanes of an access on
 // distinct banks (a 128-byte stride piles them 8 deep on the same ones).
 // Narrow rows are bound by their per-logit passes instead, where the padded
@@ -61,13 +62,13 @@ struct PC {
 };
 // Rows resident per CU: six of 256 threads (the many-row launches, where more
 // rows in flight hide the passes' latency: 80 VGPRs), four otherwise.
-template <int R, int PT>
+template <int PT>
 constexpr int rows_per_cu() { return PT == 256 ? 6 : 4; }
 // Candidate keys per target kept in LDS: 512 in the 256-thread rows, so that
 // six of them fit a CU's LDS, else 2048.  (Ragged batch of 64 sequences of up
-// to 4096 tokens, 21504 rows: four rows per CU with 2048 keys 274 us, five with 1024
-// 245, six with 512 226.)
-template <int R, int PT>
+// to 4096 tokens, 21504 rows: four rows per CU with 2048 keys 274 us, five with
+// 1024 245, six with 512 226.)
+template <int PT>
 constexpr int cand_cap() { return PT == 256 ? 512 : 2048; }
 // Slots of a long row per workgroup exchange (and in flight while a group is
 // compacted)
@@ -705,7 +706,7 @@ __device__ __forceinline__ void offsets(const PartArgs &a, const RowCtx &r, int 
 // first), then each wave writes its members at its base + mbcnt.
 template <int R, int PT, bool kRecent, bool kProb, bool kSplit, bool kHeld>
 struct Step3 {
-  PartShared<PT, cand_cap<R, PT>()> &sh;
+  PartShared<PT, cand_cap<PT>()> &sh;
   const PartArgs &a;
   const RowCtx &r;
   const Row<R, PT, kRecent, kProb> &row;
@@ -810,9 +811,9 @@ struct Step3 {
 };
 
 template <bool kMerge, int R, int PT, bool kRecent, bool kProb = false>
-__global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(rows_per_cu<R, PT>())))
+__global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(rows_per_cu<PT>())))
 void partition_kernel(PartArgs a) {
-  __shared__ PartShared<PT, cand_cap<R, PT>()> sh;
+  __shared__ PartShared<PT, cand_cap<PT>()> sh;
   RowCtx r;
   row_setup(a, r);
   Row<R, PT, kRecent, kProb> row;
@@ -889,24 +890,37 @@ hipError_t launch_pt(const PartArgs &a, int rows, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Many rows (several per CU): 256 threads each, so that more rows are
-// resident at once; few rows: 512 threads, so that each finishes sooner;
-// at most one row per CU: 1024.
+// Many rows (several per CU): 256 threads each, so that more rows are resident
+// at once (1344 rows of 2500 tokens 17.6 us, 19.8 with 512 threads; of 5000 37.4
+// and 38.3); fewer: 512 threads, so that each finishes sooner (Qwen2-7B step of
+// two sequences of 4096 tokens, 672 rows: 107.0 us, 109.6 with 256); at most one
+// row per CU: 1024.
 constexpr int kManyRows = 4 * 256;
 
 template <bool kMerge, bool kProb = false>
 hipError_t launch_rows(const PartArgs &a, int rows, hipStream_t st) {
   if (a.k_recent) {
+    // (Rows that end in recent tokens have two widths.  Long rows of 256 threads
+    // are slower with them: Qwen2-7B steps of two sequences of 8192 tokens 184 us
+    // against 177, of 20000 419 against 407.  Rows of 1024 threads would give 112
+    // rows of 8000 tokens 13.7 us against 14.3, but of 2500 8.8 against 8.5 and of
+    // 700 7.3 against 6.3.)
     if (rows >= kManyRows) return launch_pt<kMerge, 256, true, kProb>(a, rows, st);
     return launch_pt<kMerge, 512, true, kProb>(a, rows, st);
   }
   // many rows, or rows long enough to be re-read per pass even at 256
   // threads (six of them per CU) and enough of them to fill the CUs that way
-  // (the 672 rows of 65536 tokens of the Qwen2-72B step: 0.147 -> 0.143 ms)
+  // (the 672 rows of 65536 tokens of the Qwen2-72B step: 0.147 -> 0.143 ms; of
+  // 20000 tokens in a Qwen2-7B step: no difference.  From 5121 to 8192 tokens, which
+  // 512 threads hold in registers, those are the faster now: two sequences of 8192
+  // tokens 176 us a step against 185)
   if (rows >= kManyRows || (rows >= 512 && a.n_cap > 20 * 256))
     return launch_pt<kMerge, 256, false, kProb>(a, rows, st);
-  // at most one row per CU: 1024 threads shorten each row's passes
-  // (with more rows some CUs would run two of them in turn)
+  // at most one row per CU: 1024 threads shorten the passes of long rows (112
+  // rows of 8000 tokens 14.9 us, 16.3 with 512 threads; of 2500 8.8 and 8.4, of
+  // 700 7.2 and 6.2).  Two such rows per CU, held to 64 registers, are slower than
+  // two of 512 threads (336 rows of 2500 tokens 11.3 us against 9.7, of 8192 18.8
+  // against 17.7)
   if (rows <= 256 && a.n_cap <= kWideMaxR * 1024)
     return launch_pt<kMerge, 1024, false, kProb>(a, rows, st);
   return launch_pt<kMerge, 512, false, kProb>(a, rows, st);
